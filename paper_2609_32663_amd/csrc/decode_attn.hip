@@ -125,19 +125,6 @@ __device__ __forceinline__ void widen16(const u32x4& w, float* out) {
   }
 }
 
-// Workgroup that owns flat row x when `total` rows are cut into P slices
-// [floor(w*total/P), floor((w+1)*total/P)).
-// The quotient comes from an fp64 division (the numerator is below 2^53) and
-// is corrected by one where rounding crossed an integer; a 64-bit integer
-// division is a long emulated sequence.
-__device__ __forceinline__ int64_t owner_of(int64_t x, int64_t total, int64_t P) {
-  const int64_t num = (x + 1) * P - 1;
-  int64_t w = (int64_t)((double)num / (double)total);
-  if (w * total > num) --w;
-  else if ((w + 1) * total <= num) ++w;
-  return w < P - 1 ? w : P - 1;
-}
-
 template <int W>
 __device__ __forceinline__ float group_max(float x) {
 #pragma unroll

@@ -104,6 +104,19 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* tmp,
   return excl;
 }
 
+// Workgroup that owns flat row x when `total` rows are cut into P slices
+// [floor(w*total/P), floor((w+1)*total/P)).
+// The quotient comes from an fp64 division (the numerator is below 2^53) and
+// is corrected by one where rounding crossed an integer; a 64-bit integer
+// division is a long emulated sequence.
+__device__ __forceinline__ int64_t owner_of(int64_t x, int64_t total, int64_t P) {
+  const int64_t num = (x + 1) * P - 1;
+  int64_t w = (int64_t)((double)num / (double)total);
+  if (w * total > num) --w;
+  else if ((w + 1) * total <= num) ++w;
+  return w < P - 1 ? w : P - 1;
+}
+
 // Number of nonzero bytes in a 32-bit word.
 __device__ __forceinline__ int nonzero_bytes(uint32_t x) {
   uint32_t y = ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x;

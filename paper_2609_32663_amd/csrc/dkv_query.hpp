@@ -34,6 +34,13 @@ struct QueryParams {
   // the records [max_items][kQueryRowsPerWG][d + 2] (max, sum, output).
   int32_t* plan;
   float* rec;
+  // Short blocks (rows <= kShortRows) only: workgroups of the split (0: no
+  // split, one workgroup per segment), rows of a record (a multiple of 4;
+  // record slot x holds rec_rows maxima, sums and then outputs of d floats),
+  // and per segment the first record slot and the piece count.
+  int32_t P, rec_rows;
+  int32_t stream_once;     // load K and V past the caches
+  int32_t* seg_meta;
 };
 
 // How a call is split, from the shapes and the caller's hint of the total
@@ -47,6 +54,14 @@ struct QueryPlanShape {
 };
 
 QueryPlanShape query_plan_shape(int32_t nseg, int32_t rows, int32_t head_dim, int64_t rows_hint);
+// Short blocks: most query rows per segment, and most segments of a call.
+constexpr int kShortRows = 256;
+constexpr int kShortSegments = 512;
+// K and V of a call up to this size may still be in the 256 MB last-level
+// cache from the call before (the block's append, the last step), so they are
+// loaded normally; larger ones are streamed past the caches.
+constexpr int64_t kShortCachedBytes = 96 << 20;
+hipError_t launch_query_short(const QueryParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_query_attn(const QueryParams& p, int head_dim, int64_t grid, hipStream_t stream);
 
 }  // namespace dkv

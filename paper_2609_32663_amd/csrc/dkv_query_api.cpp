@@ -92,6 +92,23 @@ dkv_status dkv_query_attn(dkv_dtype dtype, int32_t batch, int32_t num_q_heads, i
   p.max_items = (int32_t)sh.max_items;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
   p.out = out;
+  if (p.rows <= dkv::kShortRows && p.nseg <= dkv::kShortSegments) {
+    p.stream_once = rows_hint <= 0 || rows_hint > dkv::kShortCachedBytes / (4 * head_dim);
+    if (sh.plan_bytes > 0) {
+      // the workspace of the long-block split, laid out for the stream split:
+      // segment metadata, then P + nseg records of rec_rows rows
+      const size_t meta = ((size_t)p.nseg * 2 * sizeof(int32_t) + 255) / 256 * 256;
+      p.rec_rows = (p.rows + 3) / 4 * 4;
+      const int64_t slots = (int64_t)((need - meta) / ((size_t)p.rec_rows * (head_dim + 2) * sizeof(float)));
+      int64_t P = rows_hint > 0 ? (rows_hint + 127) / 128 : 256;
+      if (P > 256) P = 256;
+      if (P > slots - p.nseg) P = slots - p.nseg;
+      p.P = (int32_t)P;
+      p.seg_meta = static_cast<int32_t*>(workspace);
+      p.rec = reinterpret_cast<float*>(static_cast<char*>(workspace) + meta);
+    }
+    return dkv::launch_query_short(p, head_dim, (hipStream_t)stream) == hipSuccess ? DKV_OK : DKV_ERR_HIP;
+  }
   if (sh.plan_bytes > 0) {
     p.plan = static_cast<int32_t*>(workspace);
     p.rec = reinterpret_cast<float*>(static_cast<char*>(workspace) + sh.plan_bytes);

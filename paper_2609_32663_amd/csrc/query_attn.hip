@@ -56,7 +56,7 @@
 #include <type_traits>
 
 #include "dkv_device.hpp"
-#include "dkv_query.hpp"
+#include "dkv_query_device.hpp"
 
 namespace dkv {
 
@@ -67,13 +67,7 @@ constexpr int kRG = 2;                   // 16-row groups per wave
 constexpr int kQRows = kQueryRowsPerWG;  // query rows per workgroup
 static_assert(kQRows == kQThreads / kWave * 16 * kRG, "rows per workgroup");
 constexpr int kQKeys = 64;               // keys per tile
-constexpr float kLazy = 8.f;             // log2 headroom of the lazy running max
 constexpr int kPlanThreads = 1024;
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 template <int D>
 struct QCfg {
@@ -85,38 +79,6 @@ struct QCfg {
   static constexpr int kRec = D + 2;        // floats per partial record row
   static_assert(kDma >= 1, "a tile needs one direct load per wave at least");
 };
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t q_rsrc(const char* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(((uint64_t)hi << 32) | lo), (short)0,
-                                           (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
-
-__device__ __forceinline__ int64_t q_uniform64(int64_t x) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Two probabilities as a bf16 pair (round to nearest even) and the bf16 pair
-// of what that rounding left out: a + b carries ~16 significant bits.
-__device__ __forceinline__ void bf16_split(float x0, float x1, uint32_t& a, uint32_t& b) {
-  const f32x2 x = {x0, x1};
-  const bf16x2 h = __builtin_convertvector(x, bf16x2);
-  const bf16x2 l = __builtin_convertvector(x - __builtin_convertvector(h, f32x2), bf16x2);
-  a = __builtin_bit_cast(uint32_t, h);
-  b = __builtin_bit_cast(uint32_t, l);
-}
-
-// Maximum over the lanes that share (lane % 16).
-__device__ __forceinline__ float row4_max(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
 
 // Key tiles of segment s for its last query row (the most any row sees).
 // A negative length marks a segment dkv_compact could not pack: no tiles.

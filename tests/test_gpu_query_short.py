@@ -1,0 +1,44 @@
+"""GPU parity of dkv_query_attn on short blocks (at most 256 query rows per
+segment), which take a kernel of their own: row counts at the edges of its
+row and key waves, split and unsplit calls, and both load policies.
+
+The probabilities of the P V product are two bf16 parts (16 significant bits,
+relative error 2^-17 each); a row's output may be smaller than the sum of the
+products by up to about the square root of its keys (at most 6,000 here), so
+errors stay below sqrt(6000) * 2^-17 = 6e-4.
+"""
+
+import numpy as np
+import pytest
+
+from _helpers import row_rel_err
+from test_gpu_query import _run, d  # noqa: F401  (d: the library fixture)
+
+pytestmark = pytest.mark.gpu
+
+TOL = 6e-4
+
+
+@pytest.mark.parametrize("dim", [64, 128])
+@pytest.mark.parametrize("G,n_q", [(1, 1), (16, 1), (16, 2), (1, 32), (1, 33), (4, 16), (5, 13), (8, 16), (3, 43),
+                                   (16, 16), (1, 255), (7, 37)])
+@pytest.mark.parametrize("T", [31, 700, 9000])
+def test_row_edges(d, dim, G, n_q, T):  # noqa: F811
+    """1 to 259 rows (the last one past the short kernels), keys from less
+    than a tile to many slices per segment, the block longer than a tile."""
+    rng = np.random.default_rng([dim, G, n_q, T])
+    got, want = _run(d, rng, 1, 3, G, T, dim, 0.6, 2, n_q, cap=n_q + 5)
+    assert np.isfinite(got).all()
+    assert row_rel_err(got.reshape(-1, dim), want.reshape(-1, dim)) <= TOL
+
+
+@pytest.mark.parametrize("G,n_q", [(4, 3), (4, 12), (4, 30), (4, 60)])
+@pytest.mark.parametrize("hint", [1 << 20, 4096, 0], ids=["streamed", "few", "unknown"])
+def test_hints(d, G, n_q, hint):  # noqa: F811
+    """A hint past the last-level cache's share selects the streamed loads, a
+    small one few workgroups (long slices over several segments), none the
+    widest split; some segments are empty."""
+    rng = np.random.default_rng([7, n_q, hint % 1000])
+    keep = rng.permutation(np.array([0.0, 0.02, 0.3, 0.9, 1.0, 0.5])).reshape(2, 3, 1)
+    got, want = _run(d, rng, 2, 3, G, 5000, 128, keep, 1, n_q, hint=hint)
+    assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= TOL
