@@ -123,33 +123,163 @@ __device__ __forceinline__ int nonzero_bytes(uint32_t x) {
   return __popc(y & 0x80808080u);
 }
 
-// Bit e set when byte e of the 16 bytes is nonzero.
+// Bit e set when byte e of the 16 bytes is nonzero: a word's four flags,
+// gathered by a dot product of bytes with the bits' values.
 __device__ __forceinline__ uint32_t nonzero_byte_bits(u32x4 w) {
+  uint32_t f[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) f[q] = ((((w[q] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w[q]) >> 7) & 0x01010101u;
+  const uint32_t lo = __builtin_amdgcn_udot4(f[1], 0x80402010u, __builtin_amdgcn_udot4(f[0], 0x08040201u, 0u, false), false);
+  const uint32_t hi = __builtin_amdgcn_udot4(f[3], 0x80402010u, __builtin_amdgcn_udot4(f[2], 0x08040201u, 0u, false), false);
+  return hi << 8 | lo;
+}
+
+// Inclusive sum over the lanes of a wave: prefixes inside each 16-lane row by
+// row shifts, then the last lane of rows 0 and 2 into the rows after them and
+// of row 1 into rows 2 and 3.
+template <int CTRL, int ROWS, int BANKS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, BANKS, false);
+}
+
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+  x = dpp_add<0x111, 0xF, 0xF>(x);  // row_shr:1
+  x = dpp_add<0x112, 0xF, 0xF>(x);  // row_shr:2
+  x = dpp_add<0x114, 0xF, 0xE>(x);  // row_shr:4
+  x = dpp_add<0x118, 0xF, 0xC>(x);  // row_shr:8
+  x = dpp_add<0x142, 0xA, 0xF>(x);  // row_bcast:15
+  x = dpp_add<0x143, 0xC, 0xF>(x);  // row_bcast:31
+  return x;
+}
+
+// Bit h set when query head h of a group keeps bin k; prow is the group's
+// first pattern row (rows of D bytes).  Eight heads' loads are in flight at a
+// time (heads past G repeat the last row): one load per memory round trip
+// made eight heads cost six microseconds of a map call.
+__device__ __forceinline__ uint32_t group_bits(const uint8_t* prow, int D, int G, int k) {
   uint32_t bits = 0;
+  for (int h0 = 0; h0 < G; h0 += 8) {
+    uint32_t b[8];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t x = w[q];
+    for (int e = 0; e < 8; ++e) b[e] = prow[(int64_t)(h0 + e < G ? h0 + e : G - 1) * D + k];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) bits |= (((x >> (8 * b)) & 0xFFu) != 0u ? 1u : 0u) << (4 * q + b);
+    for (int e = 0; e < 8; ++e) bits |= (h0 + e < G && b[e] != 0 ? 1u : 0u) << (h0 + e);
   }
   return bits;
 }
 
-// The 16 mask bytes of positions [j0, j0+16) of one mask row, zero beyond T
-// (16-byte loads when every row starts 16-byte aligned, bytes otherwise).
-__device__ __forceinline__ u32x4 load_mask16(const uint8_t* row, int64_t j0, int32_t T) {
+// The 16 mask bytes of positions [j0, j0 + 16) of mask row `row` (rows of T
+// bytes, `rows` of them, the first 16-byte aligned), zero beyond T; j0 is a
+// multiple of 16.  Rows of odd lengths take the two aligned 16-byte blocks
+// that hold the bytes (16 byte loads took the count and list passes of a
+// 32 x 9,001 mask from 3.1 and 4.9 us to 3.9 and 5.7); only where a block
+// would reach past the mask are the bytes read one by one.
+__device__ __forceinline__ u32x4 load_mask16(const uint8_t* mask, int64_t row, int64_t rows, int64_t j0, int32_t T) {
   u32x4 w = {0u, 0u, 0u, 0u};
-  if ((T & 15) == 0) {
-    if (j0 < T) w = *reinterpret_cast<const u32x4*>(row + j0);
-  } else {
+  if (j0 >= T) return w;
+  const int64_t f = row * T + j0;
+  const int sh = (int)(f & 15);  // the same for the whole row
+  if (sh == 0 && j0 + 16 <= T) return *reinterpret_cast<const u32x4*>(mask + f);
+  if (f - sh + 32 <= rows * T) {
+    const u32x4* at = reinterpret_cast<const u32x4*>(mask + (f - sh));
+    const u32x4 x = at[0], y = at[1];
+    const uint32_t v[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    const int b = sh & 3;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int64_t j = j0 + e;
-      const uint32_t b = (j < T && row[j] != 0) ? 1u : 0u;
-      w[e >> 2] |= b << (8 * (e & 3));
+    for (int d = 0; d < 4; ++d)
+      if ((sh >> 2) == d) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = __builtin_amdgcn_alignbyte(v[q + d + 1 < 8 ? q + d + 1 : 7], v[q + d], b);
+      }
+    const int64_t left = T - j0;  // bytes of the next row are not this row's
+    if (left < 16) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = (int)left - 4 * q;
+        if (n <= 0) w[q] = 0u;
+        else if (n < 4) w[q] &= (1u << (8 * n)) - 1u;
+      }
     }
+    return w;
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int64_t j = j0 + e;
+    const uint32_t c = (j < T && mask[row * T + j] != 0) ? 1u : 0u;
+    w[e >> 2] |= c << (8 * (e & 3));
   }
   return w;
+}
+
+// ---------------------------------------------------------------------------
+// Ranks over a mask row that one workgroup of kSweepThreads walks in sweeps
+// of 16 positions per thread, kSweeps of them at a time (all their loads in
+// flight together).
+// ---------------------------------------------------------------------------
+constexpr int kSweepThreads = 1024;
+constexpr int kSweeps = 8;
+constexpr int kSweepPositions = kSweepThreads * 16;
+constexpr int64_t kPanelPositions = (int64_t)kSweeps * kSweepPositions;
+
+// Keep bits of this thread's runs of a panel (bit e: position e of the run is
+// kept).  Whole-row-aligned masks (T a multiple of 16) have all loads in
+// flight together; others take two blocks per run, two runs at a time.
+__device__ __forceinline__ void panel_bits(const uint8_t* mask, int64_t row, int64_t rows, int64_t base, int32_t T,
+                                           uint32_t (&keep)[kSweeps]) {
+  const int64_t j = base + (int64_t)threadIdx.x * 16;
+  if ((T & 15) == 0) {
+    u32x4 w[kSweeps];
+    const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int c = 0; c < kSweeps; ++c) {
+      const int64_t j0 = j + c * kSweepPositions;
+      w[c] = j0 < T ? *reinterpret_cast<const u32x4*>(mask + row * T + j0) : z;
+    }
+#pragma unroll
+    for (int c = 0; c < kSweeps; ++c) keep[c] = nonzero_byte_bits(w[c]);
+  } else {
+#pragma unroll
+    for (int c = 0; c < kSweeps; c += 2) {
+      const u32x4 x = load_mask16(mask, row, rows, j + c * kSweepPositions, T);
+      const u32x4 y = load_mask16(mask, row, rows, j + (c + 1) * kSweepPositions, T);
+      keep[c] = nonzero_byte_bits(x);
+      keep[c + 1] = nonzero_byte_bits(y);
+      __builtin_amdgcn_sched_barrier(0);  // two runs at a time: 1,024 threads have 128 registers
+    }
+  }
+}
+
+// cnt[c] (at most 16) becomes the number of marks before this thread's in
+// sweep c, sweep-major; returns the marks of all sweeps.  `tmp` holds
+// kSweeps * kSweepThreads / 64 words of LDS, free again after the caller's
+// next barrier.  Called by every thread of the workgroup.
+__device__ __forceinline__ int sweep_ranks(int (&cnt)[kSweeps], int32_t* tmp) {
+  constexpr int NW = kSweepThreads / kWave;
+  static_assert(NW * kSweeps == 2 * kWave, "two wave totals per lane");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+#pragma unroll
+  for (int c = 0; c < kSweeps; c += 2) {  // two 16-bit sums per scan
+    const uint32_t own = (uint32_t)cnt[c] | (uint32_t)cnt[c + 1] << 16;
+    uint32_t x = wave_inclusive_sum(own);
+    if (lane == kWave - 1) {
+      tmp[c * NW + wave] = (int32_t)(x & 0xFFFFu);
+      tmp[(c + 1) * NW + wave] = (int32_t)(x >> 16);
+    }
+    x -= own;
+    cnt[c] = (int)(x & 0xFFFFu);
+    cnt[c + 1] = (int)(x >> 16);
+  }
+  __syncthreads();
+  const int a = tmp[2 * lane], b = tmp[2 * lane + 1];
+  const int inc = (int)wave_inclusive_sum((uint32_t)(a + b));
+  const int ex = inc - a - b;
+#pragma unroll
+  for (int c = 0; c < kSweeps; ++c) {
+    const int at = (c * NW + wave) >> 1;
+    cnt[c] += __builtin_amdgcn_readlane(ex, at) + ((wave & 1) ? __builtin_amdgcn_readlane(a, at) : 0);
+  }
+  return __builtin_amdgcn_readlane(inc, kWave - 1);
 }
 
 }  // namespace dkv

@@ -34,11 +34,19 @@ hipError_t launch_map_pattern(const MapParams& p, int num_segments, hipStream_t 
 
 // ---------------------------------------------------------------- compaction
 constexpr int kCompactTile = 4096;  // positions per compaction tile (count, scan and list)
-// Packed rows one copy workgroup moves (8 KiB of K or V at d = 128, bf16):
-// short workgroups copy fastest on this part (the block gather's chunk size).
+// Copy chunks of the limits' check: 32 packed rows.  The copy itself moves
+// 8 KiB of K or V per workgroup (64 rows of 128 bytes, 32 of 256, 16 of 512):
+// short workgroups copy fastest on this part until their set-up dominates
+// (4 layers of 8 x 131,072 rows, 35% kept, map and pack: 128-byte rows 213 us
+// with 16 rows, 156 with 32, 138 with 64, 145 with 128; 256-byte rows 304,
+// 255, 263, 277; two layers of 512-byte rows 259, 262, 269, 273).
 constexpr int kCopyRows = 32;
 // Copy chunks per segment: the most rows a segment can keep is T.
 inline int64_t compact_chunks(int64_t T) { return (T + kCopyRows - 1) / kCopyRows; }
+
+// Whether one workgroup per segment walks its whole mask row, or the
+// workgroups take 4096-position tiles.
+bool rank_whole_segments(int32_t T, int64_t nseg);
 
 struct CompactParams {
   const uint8_t* mask;     // [nseg][T]

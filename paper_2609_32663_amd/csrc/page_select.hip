@@ -9,10 +9,16 @@
 // page; decode reads those slots in place.  With the paper's 128-token bins
 // and 128-row pages every context entry is a whole page.
 //
-// Two passes over the (segment, 4096-position tile) grid:
-//   count  each thread turns 16 mask bytes into a 16-bit keep mask; a run
-//          starts at a kept position whose predecessor is not kept or that
-//          opens a page; the tile sums its starts and kept positions;
+// A run starts at a kept position whose predecessor is not kept or that opens
+// a page.  Contexts of up to kPanelPositions (131,072), or four times that with
+// 64 segments or more, take one workgroup per segment and one pass over the
+// mask (page_select_kernel): 256 segments of 131,072 positions, map included,
+// took 49.7 us in the two passes below and take 25.8 (14.0 for the selection
+// alone, against 39).  With fewer or longer segments one workgroup each would
+// leave the chip idle; those take two passes over the (segment, 4096-position
+// tile) grid:
+//   count  each thread turns 16 mask bytes into a 16-bit keep mask; the tile
+//          sums its run starts and kept positions;
 //   emit   each workgroup adds up the run counts of its segment's earlier
 //          tiles (its first entry), and each thread writes the entries whose
 //          runs start in its 16 positions (page, logical page, lo) and the
@@ -20,11 +26,9 @@
 //          start's rank.  The segment's last tile also writes the retained
 //          length, the append region's entries (appended tokens are always
 //          kept) and the entry count.
-// (A separate scan pass, one thread per segment walking its tiles, took
-// ~20 us of dependent loads; the prefix inside emit is one round trip.)
-// Contexts of more than kSumTiles tiles (4M positions) keep that scan pass:
-// there every emit workgroup summing all earlier tiles would cost work
-// quadratic in the context length.
+// Contexts of more than kSumTiles tiles (4M positions) have a scan pass
+// between them: there every emit workgroup summing all earlier tiles would
+// cost work quadratic in the context length.
 // A context of length 0 has no tile: one small kernel writes those segments.
 // Page sizes are multiples of 16 that divide the tile, so a page boundary is
 // always the boundary of a thread's 16 positions, and every wave's first
@@ -52,7 +56,7 @@ struct RunBits {
 __device__ __forceinline__ RunBits run_bits(const PageSelectParams& p, int seg, int tile) {
   const int tid = threadIdx.x;
   const int64_t j0 = (int64_t)tile * kCompactTile + tid * kPerThread;
-  const uint32_t keep = nonzero_byte_bits(load_mask16(p.mask + (int64_t)seg * p.T, j0, p.T));
+  const uint32_t keep = nonzero_byte_bits(load_mask16(p.mask, seg, p.nseg, j0, p.T));
   const uint32_t left = __shfl_up(keep, 1, kWave);
   const uint32_t right = __shfl_down(keep, 1, kWave);
   const bool page_first = (j0 % p.page_rows) == 0;
@@ -201,6 +205,109 @@ __global__ __launch_bounds__(kThreads) void page_emit_kernel(PageSelectParams p)
   }
 }
 
+// One workgroup per segment, the whole selection in one pass over the mask:
+// every thread holds the keep bits of kSweeps runs of 16 positions (all their
+// loads in flight at once), ranks its run starts over the segment and writes
+// the entries; the page flags are gathered in LDS and stored once.  A 16-run
+// lies in one page, so a thread needs one page number per run.
+constexpr int kUsedPages = (int)(kPanelPositions / 32);  // most pages of a panel
+
+__global__ __launch_bounds__(kSweepThreads) void page_select_kernel(PageSelectParams p) {
+  __shared__ int32_t tmp[kSweeps * kSweepThreads / kWave];
+  __shared__ int32_t kept_sum[kSweepThreads / kWave];
+  __shared__ __align__(16) uint8_t used[kUsedPages];
+  const int seg = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int pr = p.page_rows;
+  const int sh = __builtin_ctz(pr);  // page sizes are powers of two
+  const int32_t* table = p.table + (int64_t)seg * p.pages_per_seg;
+  int32_t* ent = p.entries + (int64_t)seg * p.max_entries * 4;
+  int32_t first = 0;  // entries of the panels before
+  int32_t kept = 0;
+  for (int64_t base = 0; base < p.T; base += kPanelPositions) {
+    uint32_t starts[kSweeps], ends[kSweeps];
+    int rank[kSweeps];
+    uint32_t bits[kSweeps];
+    panel_bits(p.mask, seg, p.nseg, base, p.T, bits);
+    if (p.page_used != nullptr)
+      for (int i = tid; i < kUsedPages / 4; i += kSweepThreads) reinterpret_cast<uint32_t*>(used)[i] = 0u;
+    int32_t page[kSweeps];
+#pragma unroll
+    for (int c = 0; c < kSweeps; ++c) {
+      const int64_t j0 = base + c * kSweepPositions + tid * 16;
+      const uint32_t keep = bits[c];
+      const uint32_t left = __shfl_up(keep, 1, kWave);
+      const uint32_t right = __shfl_down(keep, 1, kWave);
+      const uint32_t prev = (j0 & (pr - 1)) == 0 ? 0u : (left >> 15) & 1u;
+      const uint32_t next = ((j0 + 16) & (pr - 1)) == 0 ? 0u : right & 1u;
+      starts[c] = keep & ~((keep << 1) | prev);
+      ends[c] = keep & ~((keep >> 1) | (next << 15));
+      kept += __popc(keep);
+      rank[c] = __popc(starts[c]);
+      page[c] = starts[c] != 0u ? table[j0 >> sh] : 0;
+    }
+    const int runs = sweep_ranks(rank, tmp);  // its barrier also follows the clearing of `used`
+#pragma unroll
+    for (int c = 0; c < kSweeps; ++c) {
+      const int64_t j0 = base + c * kSweepPositions + tid * 16;
+      const int32_t lp = (int32_t)(j0 >> sh);
+      const int32_t slot0 = (int32_t)(j0 & (pr - 1));
+      uint32_t st = starts[c], en = ends[c];
+      const int64_t e0 = (int64_t)first + rank[c];
+      if (st != 0u && p.page_used != nullptr) used[lp - (int32_t)(base >> sh)] = 1;
+      for (int64_t e = e0; st != 0u; st &= st - 1u, ++e)
+        if (e < p.max_entries) {
+          *reinterpret_cast<int2*>(ent + e * 4) = int2{page[c], lp};
+          ent[e * 4 + 2] = slot0 + __builtin_ctz(st);
+        }
+      // the run ending at bit b is the last one started at or before b
+      for (; en != 0u; en &= en - 1u) {
+        const int b = __builtin_ctz(en);
+        const int64_t e = e0 + __popc(starts[c] & ((2u << b) - 1u)) - 1;
+        if (e < p.max_entries) ent[e * 4 + 3] = slot0 + b + 1;
+      }
+    }
+    first += runs;
+    __syncthreads();  // flags complete; tmp free
+    if (p.page_used != nullptr) {
+      const int64_t pg0 = base >> sh;
+      int64_t n = (kPanelPositions >> sh) < p.pages_per_seg - pg0 ? (kPanelPositions >> sh) : p.pages_per_seg - pg0;
+      uint8_t* out = p.page_used + (int64_t)seg * p.pages_per_seg + pg0;
+      for (int64_t i = tid; i < n; i += kSweepThreads) out[i] = used[i];
+      __syncthreads();  // the flags are cleared again for the next panel
+    }
+  }
+  // retained length; the append region [T, T + cap), one entry per page it
+  // touches; flags of the pages past the panels (the append region's pages
+  // are marked last: a panel's flags may cover the first of them)
+  const int wave = tid / kWave;
+  for (int o = kWave / 2; o > 0; o >>= 1) kept += __shfl_xor(kept, o, kWave);
+  if ((tid & (kWave - 1)) == 0) kept_sum[wave] = kept;
+  const int64_t a0 = (int64_t)p.T >> sh, a1 = p.cap > 0 ? ((int64_t)p.T + p.cap - 1) >> sh : a0 - 1;
+  if (p.page_used != nullptr) {
+    const int64_t panels = (p.T + kPanelPositions - 1) / kPanelPositions;
+    uint8_t* out = p.page_used + (int64_t)seg * p.pages_per_seg;
+    for (int64_t lp = panels * (kPanelPositions >> sh) + tid; lp < p.pages_per_seg; lp += kSweepThreads) out[lp] = 0;
+  }
+  __syncthreads();
+  for (int64_t lp = a0 + tid; lp <= a1; lp += kSweepThreads) {
+    const int64_t e = first + (lp - a0);
+    if (e < p.max_entries) {
+      const int64_t lo = p.T > (lp << sh) ? p.T - (lp << sh) : 0;
+      const int64_t end = (int64_t)p.T + p.cap - (lp << sh);
+      *reinterpret_cast<int4*>(ent + e * 4) =
+          int4{table[lp], (int32_t)lp, (int32_t)lo, (int32_t)(end < pr ? end : pr)};
+    }
+    if (p.page_used != nullptr) p.page_used[(int64_t)seg * p.pages_per_seg + lp] = 1;
+  }
+  if (tid == 0) {
+    int32_t n = 0;
+    for (int i = 0; i < kSweepThreads / kWave; ++i) n += kept_sum[i];
+    p.seg_len[seg] = n;
+    p.n_entries[seg] = (int32_t)(first + (a1 - a0 + 1));
+  }
+}
+
 // Segments of a context of length 0: no retained position, only the append
 // region.
 __global__ __launch_bounds__(kThreads) void page_empty_kernel(PageSelectParams p) {
@@ -219,7 +326,9 @@ size_t page_select_workspace_bytes(int64_t nseg, int64_t T) {
 
 hipError_t launch_page_select(PageSelectParams p, hipStream_t stream) {
   if (p.nseg == 0) return hipSuccess;
-  if (p.ntiles > 0) {
+  if (p.ntiles > 0 && rank_whole_segments(p.T, p.nseg)) {
+    hipLaunchKernelGGL(page_select_kernel, dim3(p.nseg), dim3(kSweepThreads), 0, stream, p);
+  } else if (p.ntiles > 0) {
     // workspace: tile counts, kept positions, and for long contexts each tile's first entry
     p.tile_base = p.ntiles > kSumTiles ? p.tile_kept + (int64_t)p.nseg * p.ntiles : nullptr;
     hipLaunchKernelGGL(page_count_kernel, dim3(p.ntiles, p.nseg), dim3(kThreads), 0, stream, p);
