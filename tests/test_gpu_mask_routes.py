@@ -1,0 +1,160 @@
+"""The mask routes' kernels at the sizes where their rules change: contexts
+around and past one workgroup's panel (131,072 positions), rows off the
+16-byte grid, bins narrower than a thread's 16 positions, and packed lengths
+at the edges of the copy's 8 KiB chunks.  Whole numbers and bytes: exact."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as o
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def d():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2609_32663_amd as lib
+    return lib
+
+
+def _mask(nseg, T, seed):
+    """Long runs and scattered positions, an empty and a full row among them."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    runs = (torch.rand((nseg, (T + 96) // 97), generator=g, device=DEV) < 0.5).to(torch.uint8)
+    m = runs.repeat_interleave(97, dim=1)[:, :T].clone()
+    m[1::3] &= (torch.rand((m[1::3].shape[0], T), generator=g, device=DEV) < 0.9).to(torch.uint8)
+    m[0], m[-1] = 0, 7  # any nonzero byte is kept
+    return m.contiguous()
+
+
+def _select(d, mask, page_rows, cap, pages, bound):
+    nseg, T = mask.shape
+    table = torch.arange(nseg * pages, device=DEV, dtype=torch.int32).flip(0).reshape(nseg, pages).contiguous()
+    ent = torch.full((nseg, bound, 4), -5, dtype=torch.int32, device=DEV)
+    n, ln = (torch.full((nseg,), -5, dtype=torch.int32, device=DEV) for _ in range(2))
+    used = torch.full((nseg, pages), 9, dtype=torch.uint8, device=DEV)
+    ws = torch.empty(max(d.dkv_page_select_workspace_bytes(nseg, T), 16), dtype=torch.uint8, device=DEV)
+    d.dkv_page_select(mask, table, page_rows, cap, ent, n, ln, ws, page_used=used)
+    return table.cpu().numpy(), ent.cpu().numpy(), n.cpu().numpy(), ln.cpu().numpy(), used.cpu().numpy()
+
+
+@pytest.mark.parametrize("nseg,T,page_rows,cap", [(64, 131072, 32, 37), (64, 131077, 32, 0), (64, 300001, 128, 300),
+                                                  (40, 131072, 64, 1), (40, 131073, 64, 1), (3, 17, 32, 40)])
+def test_page_select_panels(d, nseg, T, page_rows, cap):
+    """One panel, two, three (64 segments walk them, 40 take the tile passes)
+    against the oracle, whose entries end where the list is cut."""
+    mask = _mask(nseg, T, nseg + T)
+    pages = -(-(T + cap) // page_rows) + 2
+    few = mask[[0, 1, nseg // 2, nseg - 1]]
+    bound = T // 8 + pages + 8
+    table, ent, n, ln, used = _select(d, mask, page_rows, cap, pages, bound)
+    pick = [0, 1, nseg // 2, nseg - 1]
+    want = o.page_select((few.cpu().numpy() != 0).astype(np.uint8), table[pick], page_rows, cap)
+    for i, s in enumerate(pick):
+        e = np.asarray(want["entries"][i]).reshape(-1, 4)
+        assert n[s] == len(e) <= bound
+        np.testing.assert_array_equal(ent[s, :len(e)], e)
+        assert (ent[s, len(e):] == -5).all()
+        assert ln[s] == want["seg_len"][i]
+        np.testing.assert_array_equal(used[s], want["page_used"][i])
+
+
+@pytest.mark.parametrize("nseg,T,dim,dtype", [(64, 131085, 64, torch.bfloat16), (2, 131072, 64, torch.float32),
+                                              (2, 131080, 128, torch.float32), (3, 9001, 128, torch.bfloat16)])
+def test_compact_panels(d, nseg, T, dim, dtype):
+    mask = _mask(nseg, T, T)
+    k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
+    v = -k
+    lay = d.make_layout(1, nseg, nseg, dim, T, 0, 0, [0, T])
+    cap = 3
+    lens = (mask != 0).sum(dim=1)
+    rows = int(lens.sum()) + nseg * cap
+    ko, vo = torch.zeros((rows, dim), dtype=dtype, device=DEV), torch.zeros((rows, dim), dtype=dtype, device=DEV)
+    off, ln = torch.empty(nseg, dtype=torch.int64, device=DEV), torch.empty(nseg, dtype=torch.int32, device=DEV)
+    src = torch.full((rows,), -1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(d.dkv_compact_workspace_bytes(lay), dtype=torch.uint8, device=DEV)
+    d.dkv_compact(lay, k, v, mask, cap, ko, vo, off, ln, ws, src_pos=src)
+    assert torch.equal(ln.long(), lens)
+    assert torch.equal(off, torch.cumsum(lens + cap, 0) - lens - cap)
+    for s in range(0, nseg, max(1, nseg // 5)):
+        pos = torch.nonzero(mask[s])[:, 0]
+        a, n = int(off[s]), int(lens[s])
+        assert torch.equal(src[a:a + n].long(), pos)
+        assert torch.equal(ko[a:a + n], k[0, s, pos]) and torch.equal(vo[a:a + n], v[0, s, pos])
+        assert (src[a + n:a + n + cap] == -1).all()
+
+
+@pytest.mark.parametrize("dim,dtype", [(64, torch.bfloat16), (64, torch.float32), (128, torch.bfloat16),
+                                       (128, torch.float32)])
+def test_copy_chunk_edges(d, dim, dtype):
+    """Kept lengths around 16, 32, 64 and 128 rows, by mask and as a block
+    gather (bins of one position: a chunk spans as many ranges as rows)."""
+    lens = [0, 1, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 190]
+    T, cap, nseg = 211, 2, len(lens)
+    rng = np.random.default_rng(dim)
+    pat = np.zeros((1, nseg, T), dtype=np.uint8)
+    for s, n in enumerate(lens):
+        pat[0, s, rng.choice(T, n, replace=False)] = 1
+    mask = torch.from_numpy(pat[0, :, ::-1].copy()).to(DEV)  # bin u is position T - 1 - u
+    k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
+    lay = d.make_layout(1, nseg, nseg, dim, T, 0, 0, list(range(T + 1)))
+    rows = sum(lens) + nseg * cap
+    got = []
+    for bins in (False, True):
+        ko, vo = torch.zeros((rows, dim), dtype=dtype, device=DEV), torch.zeros((rows, dim), dtype=dtype, device=DEV)
+        off, ln = torch.empty(nseg, dtype=torch.int64, device=DEV), torch.empty(nseg, dtype=torch.int32, device=DEV)
+        f, w = ((d.dkv_compact_bins, d.dkv_compact_bins_workspace_bytes) if bins else
+                (d.dkv_compact, d.dkv_compact_workspace_bytes))
+        ws = torch.empty(w(lay), dtype=torch.uint8, device=DEV)
+        f(lay, k, k, torch.from_numpy(pat).to(DEV) if bins else mask, cap, ko, vo, off, ln, ws)
+        assert ln.tolist() == lens
+        for s, n in enumerate(lens):
+            a = int(off[s])
+            want = k[0, s, torch.nonzero(mask[s])[:, 0]]
+            assert torch.equal(ko[a:a + n], want) and torch.equal(vo[a:a + n], want)
+        got.append(ko)
+    assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 250, 256, 4099, 16400])
+@pytest.mark.parametrize("width", [1, 2, 5, 15, 16, 40, None])
+def test_map_regions(d, T, width):
+    """Bins narrower than a run of 16 positions, rows off the 16-byte grid,
+    units of every length, edges that end before, at and past the context."""
+    rng = np.random.default_rng([T, width or 0])
+    S, R = (0, 0) if T < 16 else (int(rng.integers(0, 20)), int(rng.integers(0, 30)))
+    if width is None:
+        edges = np.concatenate([[0], np.cumsum(rng.integers(1, 9, size=min(500, T + 3)))]).tolist()
+    else:
+        edges = [width * i for i in range(max(2, min(400, T // width + int(rng.integers(0, 3)))))]
+    N, Hkv, G, D = 3, 2, 3, len(edges) - 1
+    pat = (rng.random((N, Hkv * G, D)) < 0.3).astype(np.uint8)
+    ulen = np.array([T, max(0, T - 3), T // 2], dtype=np.int32)
+    lay = d.make_layout(N, Hkv * G, Hkv, 64, T, S, R, edges)
+    for ragged in (False, True):
+        kv = torch.full((N, Hkv, T), 9, dtype=torch.uint8, device=DEV)
+        qm = torch.full((N, Hkv * G, T), 9, dtype=torch.uint8, device=DEV)
+        ln = torch.empty((N, Hkv), dtype=torch.int32, device=DEV)
+        pt = torch.from_numpy(pat).to(DEV)
+        if ragged:
+            d.dkv_map_pattern_ragged(lay, torch.from_numpy(ulen).to(DEV), pt, kv, ln, q_mask=qm)
+        else:
+            d.dkv_map_pattern(lay, pt, kv, ln, q_mask=qm)
+        want_q = np.zeros((N, Hkv * G, T), dtype=np.uint8)
+        for n in range(N):
+            t = int(ulen[n]) if ragged else T
+            for j in range(t):
+                u = t - 1 - j - R
+                if j < S or u < 0:
+                    want_q[n, :, j] = 1
+                elif u < edges[-1]:
+                    want_q[n, :, j] = pat[n, :, np.searchsorted(edges, u, side="right") - 1]
+        want = want_q.reshape(N, Hkv, G, T).max(axis=2)
+        np.testing.assert_array_equal(qm.cpu().numpy(), want_q)
+        np.testing.assert_array_equal(kv.cpu().numpy(), want)
+        np.testing.assert_array_equal(ln.cpu().numpy(), want.sum(axis=2))
