@@ -242,11 +242,8 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p) {
 
 }  // namespace
 
-<<<<<<< Updated upstream
-=======
 // One workgroup holds a panel of kPanelPositions at once; further panels are
 // walked one after the other, which pays only when the segments fill the chip.
->>>>>>> Stashed changes
 bool rank_whole_segments(int32_t T, int64_t nseg) {
   return T <= kPanelPositions * (nseg >= 64 ? 4 : 1);
 }

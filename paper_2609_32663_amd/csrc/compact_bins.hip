@@ -81,15 +81,9 @@ constexpr int kPlanTable = 4096;
 __global__ __launch_bounds__(kPlanThreads) void bins_plan_kernel(BinsParams p) {
   __shared__ int64_t red[kPlanThreads / kWave + 1];
   __shared__ int32_t tbl[kPlanTable];
-<<<<<<< Updated upstream
-  // bins kept by some query head of the group (the union), read coalesced;
-  // each thread reading its own ranges' bytes head by head, twice, took the
-  // plan of 64 segments of 1,013 bins from 5 to 16.6 us
-=======
   // bins kept by some query head of the group (the union), read coalesced
   // (each thread reading its own ranges' bytes head by head, twice, made the
   // plan 2 us longer)
->>>>>>> Stashed changes
   extern __shared__ uint8_t kept[];
   const int s = blockIdx.x;
   const int n = s / p.Hkv, g = s - n * p.Hkv;
@@ -104,11 +98,7 @@ __global__ __launch_bounds__(kPlanThreads) void bins_plan_kernel(BinsParams p) {
     const int32_t u = p.unit_len[n];
     Tn = u < 0 ? 0 : (u > p.T ? p.T : u);
   }
-<<<<<<< Updated upstream
-  for (int k = threadIdx.x; k < p.D; k += kThreads) kept[k] = group_bits(prow, p.D, p.G, k) != 0u ? 1 : 0;
-=======
   for (int k = threadIdx.x; k < p.D; k += kPlanThreads) kept[k] = group_bits(prow, p.D, p.G, k) != 0u ? 1 : 0;
->>>>>>> Stashed changes
   __syncthreads();
   auto range_kept = [&](int i) { return i == 0 || i == p.D + 1 || kept[p.D - i] != 0; };
   // this thread's ranges (consecutive, so the scans keep token order)
@@ -264,11 +254,7 @@ size_t bins_workspace_bytes(int64_t nseg, int32_t D, int32_t T) {
 }
 
 hipError_t launch_compact_bins(const BinsParams& p, hipStream_t stream) {
-<<<<<<< Updated upstream
-  hipLaunchKernelGGL(bins_plan_kernel, dim3(p.nseg), dim3(kThreads), (size_t)p.D, stream, p);
-=======
   hipLaunchKernelGGL(bins_plan_kernel, dim3(p.nseg), dim3(kPlanThreads), (size_t)p.D, stream, p);
->>>>>>> Stashed changes
   hipLaunchKernelGGL(bins_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, p);
   if (p.nchunks > 0) {
     const dim3 grid(2 * p.nchunks, p.nseg);  // a K and a V workgroup per chunk
