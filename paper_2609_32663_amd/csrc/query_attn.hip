@@ -316,12 +316,17 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
   };
 
   // Online softmax of a half whose first key is kh: the raw scores become
-  // the probabilities 2^(c s - m), m and l move on, alpha is each row's
-  // rescale factor.  The reference max m is lazy: it moves only when a
-  // half's max exceeds it by more than kLazy (log2 units), so probabilities
-  // stay below 2^kLazy and the accumulators are rescaled only then.
-  auto softmax = [&](auto masked, float (&sc)[kRG][2][4], int64_t kh, float (&alpha)[kRG])
-                     __attribute__((always_inline)) {
+  // the probabilities 2^(c s - m), m and l move on.  The reference max m is
+  // lazy: it moves only when a half's max exceeds it by more than kLazy (log2
+  // units), so probabilities stay below 2^kLazy.  One of a row's four lanes
+  // sees that by itself, so the row max across lanes, the factors and the
+  // rescale of m, l and the accumulators (output rows of a lane are queries
+  // 4kg + v of the group: their factors live in the lanes of those rows) run
+  // only in waves where some lane does: 256 tokens of an 8B layer at 128K
+  // 306.5 -> 301.1 us a call, at 32K 109.1 -> 105.8, on one box (taking the
+  // bf16 remainders by dot products as well, 16 instructions fewer per half,
+  // gave 307 and 104: the kernel runs at the power limit).
+  auto softmax = [&](auto masked, float (&sc)[kRG][2][4], int64_t kh) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < kRG; ++q) {
       // keys past a row's causal limit or past the range: only in the
@@ -339,10 +344,20 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
       for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
         for (int v = 0; v < 4; ++v) mx = fmaxf(mx, sc[q][jj][v]);
-      mx = row4_max(mx) * cpos;
-      const bool grow = mx > m[q] + kLazy;
-      alpha[q] = fast_exp2(grow ? m[q] - mx : 0.f);
-      m[q] = grow ? mx : m[q];
+      mx *= cpos;
+      if (__builtin_amdgcn_ballot_w64(mx > m[q] + kLazy)) {
+        mx = row4_max(mx);
+        const bool grow = mx > m[q] + kLazy;
+        const float alpha = fast_exp2(grow ? m[q] - mx : 0.f);
+        m[q] = grow ? mx : m[q];
+        l[q] *= alpha;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float av = __shfl(alpha, 4 * kg + v, 64);
+#pragma unroll
+          for (int b = 0; b < C::kBlocks; ++b) o[q][b][v] *= av;
+        }
+      }
       const float m_use = m[q] == -INFINITY ? 0.f : m[q];
       float ps = 0.f;
 #pragma unroll
@@ -352,28 +367,11 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
           sc[q][jj][v] = fast_exp2(__builtin_fmaf(sc[q][jj][v], cpos, -m_use));
           ps += sc[q][jj][v];
         }
-      l[q] = l[q] * alpha[q] + ps;
+      l[q] += ps;
       // an empty operand barrier: the sum is formed here, in the vector
       // phase, instead of being sunk into a later one (which unbalances the
       // phases and keeps the probabilities alive across them)
       asm volatile("" : "+v"(l[q]));
-    }
-  };
-
-  // O *= alpha per row.  Output rows of this lane are queries 4kg + v of the
-  // group: their factors live in the lanes of those rows.  The wave skips
-  // the rescale unless a factor differs from 1.
-  auto rescale = [&](const float (&alpha)[kRG]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < kRG; ++q) {
-      if (__builtin_amdgcn_ballot_w64(alpha[q] != 1.f)) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float av = __shfl(alpha[q], 4 * kg + v, 64);
-#pragma unroll
-          for (int b = 0; b < C::kBlocks; ++b) o[q][b][v] *= av;
-        }
-      }
     }
   };
 
@@ -462,12 +460,11 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
   issue(kbase, koff, k_lo + kQKeys, kbuf[1]);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   __syncthreads();
-  float sc[kRG][2][4], al[kRG];
+  float sc[kRG][2][4];
   u32x4 ph[kRG], pl[kRG];
   constexpr int kWaitOne = 0x0F70 | C::kDma;  // vmcnt(kDma): the younger of two tiles may still be in flight
   auto vphase = [&](auto masked, int64_t kh) __attribute__((always_inline)) {
-    softmax(masked, sc, kh, al);
-    rescale(al);
+    softmax(masked, sc, kh);
     split(sc, ph, pl);
   };
   // P V first: the probabilities are dead before the new scores are formed
