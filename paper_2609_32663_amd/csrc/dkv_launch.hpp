@@ -102,6 +102,7 @@ struct TopkParams {
   int64_t n;           // entries, < 2^31
   int64_t k;           // 0 <= k <= n
   int64_t chunk;       // entries per workgroup (set by the launcher)
+  int32_t copies;      // histograms per round in use (set by the launcher)
 };
 size_t topk_workspace_bytes(int64_t n);
 hipError_t launch_topk_pattern(TopkParams p, hipStream_t stream);
