@@ -146,6 +146,10 @@ def dtype_code(t):
 
 
 def _dev(t, name, optional=False):
+    # the smallest decode step is bound by this module's host time: the usual
+    # argument takes two attribute reads and one call
+    if type(t) is torch.Tensor and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if t is None:
         if optional:
             return None
@@ -157,10 +161,18 @@ def _dev(t, name, optional=False):
     return t.data_ptr()
 
 
+try:  # the current stream's handle without a Stream object around it
+    _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+except AttributeError:
+    _raw_stream = None
+
+
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _check(fn, status):
@@ -258,8 +270,7 @@ def dkv_append_decode_attn(q, k_new, v_new, n_tail, append_cap, k_c, v_c, seg_of
         dtype_code(q.dtype), B, Hq, int(num_kv_heads), d, _dev(q, "q"), _dev(k_new, "k_new"),
         _dev(v_new, "v_new"), n_new, int(n_tail), int(append_cap), _dev(k_c, "k_c"),
         _dev(v_c, "v_c"), _dev(seg_off, "seg_off"), _dev(seg_len, "seg_len"), float(sm_scale),
-        int(rows_hint), _dev(out, "out"), _dev(workspace, "workspace"),
-        workspace.numel() * workspace.element_size(), _stream(stream)))
+        int(rows_hint), _dev(out, "out"), _dev(workspace, "workspace"), workspace.nbytes, _stream(stream)))
 
 
 def dkv_append_decode_attn_noalloc(q, k_new, v_new, n_tail, append_cap, k_c, v_c, seg_off, seg_len,
