@@ -43,7 +43,7 @@ PMC_FILE = os.path.join(ROOT, "profiles", "decode_attn_llama8b_stack_128k_pmc.js
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2609_32663_amd", "csrc", f)
                for f in ("decode_attn.hip", "dkv_device.hpp", "dkv_launch.hpp")]
 QUERY_SRCS = [os.path.join(ROOT, "paper_2609_32663_amd", "csrc", f)
-              for f in ("query_attn.hip", "dkv_device.hpp", "dkv_query.hpp")]
+              for f in ("query_attn.hip", "dkv_device.hpp", "dkv_query.hpp", "dkv_query_device.hpp")]
 COMPACT_SRCS = [os.path.join(ROOT, "paper_2609_32663_amd", "csrc", f)
                 for f in ("compact.hip", "dkv_device.hpp", "dkv_launch.hpp")]
 BINS_SRCS = [os.path.join(ROOT, "paper_2609_32663_amd", "csrc", f)
@@ -370,16 +370,18 @@ def pmc_summary(fetch_csv, write_csv, bench_log, command):
         res["query_traffic_bytes_per_call"] = int(q_bytes["fetch"] + q_bytes["write"])
     if len(per_paged) == 2:
         res["paged_traffic_bytes_per_launch"] = int(per_paged["fetch"] + per_paged["write"])
-    # the headline's timed one-time compaction: the second count / scan /
-    # list / copy sequence of the run (the first is its warm-up call), against
+    # the headline's timed one-time compaction: the second count / scan / list /
+    # copy sequence of the run (the first is its warm-up call), against
     # its algorithmic bytes (retained K and V rows read and written, mask read)
     res["compact_kernel_sha256_16"] = kernel_hash(COMPACT_SRCS)
-    names = ("compact_count_kernel", "compact_scan_kernel", "compact_list_kernel", "compact_copy_kernel")
+    # (rank / scan / copy where one workgroup walks a segment's whole mask row)
+    forms = (("compact_count_kernel", "compact_scan_kernel", "compact_list_kernel", "compact_copy_kernel"),
+             ("compact_rank_kernel", "compact_scan_kernel", "compact_copy_kernel"))
     for key, path, counter in (("fetch", fetch_csv, "FETCH_SIZE"), ("write", write_csv, "WRITE_SIZE")):
         rows = pmc_per_dispatch(path, counter)
         calib = res[f"{key}_calibration"]
-        packs = [sum(rows[i + j][1] for j in range(4)) for i in range(len(rows) - 3)
-                 if all(names[j] in rows[i + j][0] for j in range(4))]
+        packs = [sum(rows[i + j][1] for j in range(len(names))) for i in range(len(rows)) for names in forms
+                 if i + len(names) <= len(rows) and all(n in rows[i + j][0] for j, n in enumerate(names))]
         if len(packs) >= 2:
             res[f"compact_{key}_bytes"] = int(packs[1] * 1024.0 * calib)
     if "compact_fetch_bytes" in res and "compact_write_bytes" in res:
