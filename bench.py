@@ -270,7 +270,7 @@ def trace_summary(trace_dir, bench_log, command):
               f"the context, every layer)",
               f"# command: {command}",
               f"# sources measured: query kernel sha256/16 {kernel_hash(QUERY_SRCS)} (query_attn.hip, "
-              f"dkv_device.hpp, dkv_query.hpp)",
+              f"dkv_device.hpp, dkv_query.hpp, dkv_query_device.hpp)",
               "# per-kernel statistics (rocprofv3 --stats; us):",
               f"{'kernel':58s} {'calls':>6s} {'avg':>9s} {'min':>9s} {'max':>9s}"]
         for r in stats:
