@@ -242,10 +242,14 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p) {
 
 }  // namespace
 
-// One workgroup holds a panel of kPanelPositions at once; further panels are
-// walked one after the other, which pays only when the segments fill the chip.
+// A workgroup walks its row in panels one after the other, so whole rows pay
+// when they are short or when the segments fill the chip: one segment per 4096
+// positions of a row.  Map and page selection, whole / tiles, us: 8 segments
+// of 32,768 14.8 / 15.2, of 131,072 15.8 / 14.8, of 262,144 23.1 / 15.2; 32 of
+// 131,072 17.3 / 17.5, of 262,144 26.8 / 22.8; 64 of 262,144 27.9 / 29.0, of
+// 524,288 47.0 / 43.4; 256 of 131,072 25.8 / 49.7.
 bool rank_whole_segments(int32_t T, int64_t nseg) {
-  return T <= kPanelPositions * (nseg >= 64 ? 4 : 1);
+  return T <= 32768 || (T <= 4 * kPanelPositions && T <= nseg * kCompactTile);
 }
 
 size_t compact_workspace_bytes(int64_t nseg, int64_t T) {

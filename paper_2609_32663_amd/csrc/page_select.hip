@@ -10,8 +10,8 @@
 // and 128-row pages every context entry is a whole page.
 //
 // A run starts at a kept position whose predecessor is not kept or that opens
-// a page.  Contexts of up to kPanelPositions (131,072), or four times that with
-// 64 segments or more, take one workgroup per segment and one pass over the
+// a page.  Short contexts, and longer ones with enough segments
+// (rank_whole_segments), take one workgroup per segment and one pass over the
 // mask (page_select_kernel): 256 segments of 131,072 positions, map included,
 // took 49.7 us in the two passes below and take 25.8 (14.0 for the selection
 // alone, against 39).  With fewer or longer segments one workgroup each would

@@ -43,11 +43,12 @@ def _select(d, mask, page_rows, cap, pages, bound):
     return table.cpu().numpy(), ent.cpu().numpy(), n.cpu().numpy(), ln.cpu().numpy(), used.cpu().numpy()
 
 
-@pytest.mark.parametrize("nseg,T,page_rows,cap", [(64, 131072, 32, 37), (64, 131077, 32, 0), (64, 300001, 128, 300),
-                                                  (40, 131072, 64, 1), (40, 131073, 64, 1), (3, 17, 32, 40)])
+@pytest.mark.parametrize("nseg,T,page_rows,cap", [(64, 131072, 32, 37), (64, 131077, 32, 0), (72, 290001, 128, 300),
+                                                  (40, 163840, 64, 1), (40, 163841, 64, 1), (4, 32768, 32, 5),
+                                                  (4, 32769, 32, 5), (3, 17, 32, 40)])
 def test_page_select_panels(d, nseg, T, page_rows, cap):
-    """One panel, two, three (64 segments walk them, 40 take the tile passes)
-    against the oracle, whose entries end where the list is cut."""
+    """One panel, two and three, and either side of the rule that sends a call
+    to the tile passes, against the oracle."""
     mask = _mask(nseg, T, nseg + T)
     pages = -(-(T + cap) // page_rows) + 2
     few = mask[[0, 1, nseg // 2, nseg - 1]]
@@ -64,8 +65,9 @@ def test_page_select_panels(d, nseg, T, page_rows, cap):
         np.testing.assert_array_equal(used[s], want["page_used"][i])
 
 
-@pytest.mark.parametrize("nseg,T,dim,dtype", [(64, 131085, 64, torch.bfloat16), (2, 131072, 64, torch.float32),
-                                              (2, 131080, 128, torch.float32), (3, 9001, 128, torch.bfloat16)])
+@pytest.mark.parametrize("nseg,T,dim,dtype", [(64, 131085, 64, torch.bfloat16), (2, 131080, 64, torch.float32),
+                                              (2, 32768, 128, torch.float32), (3, 32769, 128, torch.bfloat16),
+                                              (33, 133333, 64, torch.bfloat16), (3, 9001, 128, torch.bfloat16)])
 def test_compact_panels(d, nseg, T, dim, dtype):
     mask = _mask(nseg, T, T)
     k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
