@@ -54,9 +54,15 @@ struct QueryPlanShape {
 };
 
 QueryPlanShape query_plan_shape(int32_t nseg, int32_t rows, int32_t head_dim, int64_t rows_hint);
-// Short blocks: most query rows per segment, and most segments of a call.
+// Short blocks: most query rows per segment, and most segments of a call (the
+// workgroups' prefix over them shares the LDS with the tiles).
 constexpr int kShortRows = 256;
 constexpr int kShortSegments = 512;
+// Blocks of more than 128 rows leave one key wave and 133 KB of record per
+// piece, so they pay only over long segments: at this many keys per segment on
+// average.  Before / now, us, 240 rows: 8 segments of 11,500 keys 54.7 / 41.2,
+// of 45,000 121.3 / 87.1; 128 of 1,050 85.8 / 110.9, 480 of 1,430 193.6 / 280.4.
+constexpr int64_t kShortLongKeys = 8192;
 // K and V of a call up to this size may still be in the 256 MB last-level
 // cache from the call before (the block's append, the last step), so they are
 // loaded normally; larger ones are streamed past the caches.

@@ -1,5 +1,5 @@
-// Query-block attention for short blocks: at most kShortRows (256) query rows
-// (tokens x heads of a group) per segment.  What the rows compute is what
+// Query-block attention for short blocks: at most 128 query rows (tokens
+// x heads of a group) per segment, or kShortRows (256) over long segments.  What the rows compute is what
 // query_attn.hip computes; here the block is so short that reading K and V
 // bounds the call, so the kernel is a stream over the keys, split like the
 // decode step's, instead of 256-row query tiles.

@@ -4,8 +4,8 @@ row and key waves, split and unsplit calls, and both load policies.
 
 The probabilities of the P V product are two bf16 parts (16 significant bits,
 relative error 2^-17 each); a row's output may be smaller than the sum of the
-products by up to about the square root of its keys (at most 6,000 here), so
-errors stay below sqrt(6000) * 2^-17 = 6e-4.
+products by up to about the square root of its keys (at most 9,000 here), so
+errors stay below sqrt(9000) * 2^-17 = 7.3e-4.
 """
 
 import numpy as np
@@ -16,16 +16,17 @@ from test_gpu_query import _run, d  # noqa: F401  (d: the library fixture)
 
 pytestmark = pytest.mark.gpu
 
-TOL = 6e-4
+TOL = 7.3e-4
 
 
 @pytest.mark.parametrize("dim", [64, 128])
 @pytest.mark.parametrize("G,n_q", [(1, 1), (16, 1), (16, 2), (1, 32), (1, 33), (4, 16), (5, 13), (8, 16), (3, 43),
                                    (16, 16), (1, 255), (7, 37)])
-@pytest.mark.parametrize("T", [31, 700, 9000])
+@pytest.mark.parametrize("T", [31, 700, 9000, 14000])
 def test_row_edges(d, dim, G, n_q, T):  # noqa: F811
     """1 to 259 rows (the last one past the short kernels), keys from less
-    than a tile to many slices per segment, the block longer than a tile."""
+    than a tile to many slices per segment (blocks of more than 128 rows take
+    the short kernel at 14,000 positions only), the block longer than a tile."""
     rng = np.random.default_rng([dim, G, n_q, T])
     got, want = _run(d, rng, 1, 3, G, T, dim, 0.6, 2, n_q, cap=n_q + 5)
     assert np.isfinite(got).all()
