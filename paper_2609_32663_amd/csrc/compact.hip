@@ -36,6 +36,7 @@ namespace dkv {
 namespace {
 
 constexpr int kThreads = 256;
+static_assert(kThreads == kCopyThreads, "the dispatch limit counts the copy kernel's workgroups");
 constexpr int kPerThread = 16;
 static_assert(kThreads * kPerThread == kCompactTile, "tile = threads x 16 positions");
 
@@ -270,17 +271,16 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t stream) {
   }
   if (p.ntiles > 0) {
     if (!whole) hipLaunchKernelGGL(compact_list_kernel, grid, dim3(kThreads), 0, stream, p);
-    auto copy = [&](auto kernel, int rows) {  // a K and a V workgroup per chunk
-      hipLaunchKernelGGL(kernel, dim3((uint32_t)(2 * (((int64_t)p.T + rows - 1) / rows)), p.nseg), dim3(kThreads), 0,
-                         stream, p);
+    const int rows = copy_rows(p.T, p.row_bytes);
+    auto copy = [&](auto kernel) {  // a K and a V workgroup per chunk
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)copy_workgroups(p.T, rows), p.nseg), dim3(kThreads), 0, stream, p);
     };
     switch (p.row_bytes) {
-      case 128: copy(compact_copy_kernel<8, 64>, 64); break;
-      case 256: copy(compact_copy_kernel<16, 32>, 32); break;
+      case 128: copy(compact_copy_kernel<8, 64>); break;
+      case 256: copy(compact_copy_kernel<16, 32>); break;
       case 512:
-        // 16-row chunks while their dispatch fits 2^32 work-items
-        if (p.T <= 1 << 27) copy(compact_copy_kernel<32, 16>, 16);
-        else copy(compact_copy_kernel<32, 32>, 32);
+        if (rows == 16) copy(compact_copy_kernel<32, 16>);
+        else copy(compact_copy_kernel<32, 32>);
         break;
       default: return hipErrorInvalidValue;
     }

@@ -171,9 +171,9 @@ dkv_status dkv_compact(const dkv_layout* layout, dkv_dtype dtype, const void* k,
   if (!head_dim_ok(L.head_dim)) return DKV_ERR_UNSUPPORTED;
   const int64_t nseg = (int64_t)L.num_units * L.num_kv_heads;
   if (nseg > 65535) return DKV_ERR_UNSUPPORTED;
-  // the copy dispatch (a K and a V workgroup of 256 per 32-row chunk) must
-  // hold fewer than 2^32 work-items
-  if (2 * dkv::compact_chunks(L.context_len) * 256 > (int64_t)UINT32_MAX) return DKV_ERR_UNSUPPORTED;
+  // the copy dispatch, in 32-row chunks where shorter ones would be too many,
+  // must hold fewer than 2^32 work-items
+  if (!dkv::copy_dispatch_fits(L.context_len, dkv::kCopyRows)) return DKV_ERR_UNSUPPORTED;
   if (nseg == 0) return DKV_OK;
   if (k == nullptr || v == nullptr || kv_mask == nullptr || k_out == nullptr || v_out == nullptr ||
       seg_off == nullptr || seg_len == nullptr)

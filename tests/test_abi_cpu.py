@@ -467,3 +467,45 @@ def test_noalloc_validation():
     assert call(out=MIS) == d.DKV_ERR_MISALIGNED
     assert call(dim=96) == d.DKV_ERR_UNSUPPORTED
     assert call(B=0, q=NUL, out=NUL) == d.DKV_OK
+
+
+COPY_LIMIT = r"""
+#include "dkv_launch.hpp"
+#include <cstdio>
+int main() {
+  long long T;
+  int row_bytes;
+  while (std::scanf("%lld %d", &T, &row_bytes) == 2) {
+    const int rows = dkv::copy_rows(T, row_bytes);
+    std::printf("%d %lld\n", rows, (long long)dkv::copy_workgroups(T, rows) * 256);
+  }
+}
+"""
+
+
+def test_copy_dispatch_stays_below_2_32_work_items(tmp_path):
+    """The copy's chunk and grid over every row size, around the contexts where
+    a chunk size would reach 2^32 work-items and at the longest that
+    dkv_compact accepts: the accepted ones all fit."""
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    rocm = "/opt/rocm/include"
+    if cxx is None or not os.path.isdir(rocm):
+        pytest.skip("no host compiler or HIP headers")
+    src = tmp_path / "limit.cpp"
+    src.write_text(COPY_LIMIT)
+    exe = tmp_path / "limit"
+    subprocess.run([cxx, "-std=c++17", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}",
+                    f"-I{os.path.join(ROOT, 'paper_2609_32663_amd', 'csrc')}", f"-I{os.path.join(ROOT, 'include')}",
+                    str(src), "-o", str(exe)], check=True)
+    T = sorted({(1 << 27) + e for e in range(-33, 34)} | {(1 << 28) - e for e in range(32, 64)} |
+               {1, 16, 17, 32, 33, 64, 65, 4096})
+    cases = [(t, b) for t in T for b in (128, 256, 512)]
+    out = subprocess.run([str(exe)], input="\n".join(f"{t} {b}" for t, b in cases), check=True, capture_output=True,
+                         text=True).stdout.split("\n")
+    for (t, b), line in zip(cases, out):
+        rows, items = map(int, line.split())
+        assert items < 1 << 32, (t, b)
+        assert rows in (8192 // b, 32), (t, b)
+        assert items >= 512 * (t // rows), (t, b)
