@@ -273,7 +273,11 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
   }
   // Global -> LDS: K or V rows [kt, kt + kQKeys) of the segment into a tile
   // buffer.  Keys past k_hi (a whole tile past it included) read zeros
-  // without touching memory, so the loads are issued unconditionally.
+  // without touching memory, so the loads are issued unconditionally.  (The
+  // range check of a raw buffer counts the scalar offset too, which
+  // tests/test_gpu_query_room.py holds with NaN behind every segment; the
+  // displacement in the vector offset cost 4 registers and 1% of a 256-token
+  // call at 128K.)
   auto issue = [&](const char* base, uint32_t off, int64_t kt, uint16_t* buf) __attribute__((always_inline)) {
     const int64_t left = k_hi - kt;
     const uint32_t nk = (uint32_t)(left <= 0 ? 0 : (left < kQKeys ? left : kQKeys));
