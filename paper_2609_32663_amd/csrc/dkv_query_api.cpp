@@ -103,8 +103,8 @@ dkv_status dkv_query_attn(dkv_dtype dtype, int32_t batch, int32_t num_q_heads, i
       const size_t meta = ((size_t)p.nseg * 2 * sizeof(int32_t) + 255) / 256 * 256;
       p.rec_rows = (p.rows + 3) / 4 * 4;
       const int64_t slots = (int64_t)((need - meta) / ((size_t)p.rec_rows * (head_dim + 2) * sizeof(float)));
-      int64_t P = rows_hint > 0 ? (rows_hint + 127) / 128 : 256;
-      if (P > 256) P = 256;
+      // at least 128 keys per workgroup, up to 256 workgroups (any hint is valid)
+      int64_t P = rows_hint > 0 && rows_hint < 256 * 128 ? (rows_hint + 127) / 128 : 256;
       if (P > slots - p.nseg) P = slots - p.nseg;
       p.P = (int32_t)P;
       p.seg_meta = static_cast<int32_t*>(workspace);

@@ -10,6 +10,7 @@ errors stay below sqrt(9000) * 2^-17 = 7.3e-4.
 
 import numpy as np
 import pytest
+import torch
 
 from _helpers import row_rel_err
 from test_gpu_query import _run, d  # noqa: F401  (d: the library fixture)
@@ -43,3 +44,21 @@ def test_hints(d, G, n_q, hint):  # noqa: F811
     keep = rng.permutation(np.array([0.0, 0.02, 0.3, 0.9, 1.0, 0.5])).reshape(2, 3, 1)
     got, want = _run(d, rng, 2, 3, G, 5000, 128, keep, 1, n_q, hint=hint)
     assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= TOL
+
+
+@pytest.mark.parametrize("hint", [(1 << 63) - 1, (1 << 63) - 128, 1 << 40])
+def test_largest_hints(d, hint):  # noqa: F811
+    """Any positive hint is valid: the largest ones split the call as widely as
+    a merely large one: 256 slices of the keys and a fixed cost of 384 keys per
+    segment, of which at most 384 / 66 + 1 = 7 a segment hold no key (at least
+    16,900 keys and costs in all), and one piece more per segment boundary."""
+    seen = {}
+
+    def inspect(ws, seg_len, rows_hint, wsb):
+        meta = ws[:3 * 8].cpu().view(torch.int32).numpy().reshape(3, 2)
+        seen["first"], seen["count"] = meta[:, 0], meta[:, 1]
+
+    got, want = _run(d, np.random.default_rng(17), 1, 3, 4, 9000, 128, 0.6, 1, 3, hint=hint, inspect=inspect)
+    assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= TOL
+    assert 256 - 3 * 7 <= seen["count"].sum() <= 258
+    assert seen["first"][0] == 0 and (np.diff(seen["first"]) >= seen["count"][:-1]).all()
