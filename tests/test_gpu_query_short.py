@@ -61,4 +61,4 @@ def test_largest_hints(d, hint):  # noqa: F811
     got, want = _run(d, np.random.default_rng(17), 1, 3, 4, 9000, 128, 0.6, 1, 3, hint=hint, inspect=inspect)
     assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= TOL
     assert 256 - 3 * 7 <= seen["count"].sum() <= 258
-    assert seen["first"][0] == 0 and (np.diff(seen["first"]) >= seen["count"][:-1]).all()
+    assert 0 <= seen["first"][0] <= 7 and (np.diff(seen["first"]) >= seen["count"][:-1]).all()
