@@ -6,7 +6,6 @@
 // pattern rows are folded into one G-bit word per bin in LDS (bit h = query
 // head g*G+h keeps the bin), so the union over the group is "word != 0" and
 // the per-head decision is one bit.  Each thread then owns 16 consecutive
-// the per-head decision is one bit.  Each thread then owns 16 consecutive
 // positions per sweep and walks the regions they cross (sink, a bin, recent
 // window, uncovered, past the context; usually one): the first one's bin comes
 // from a division for uniform edges, a binary search over the edges in LDS
@@ -112,14 +111,16 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
     if (tid == 0) p.kv_len[seg] = (int32_t)(always + binned);
   }
 
-  // positions fit 31 bits (T is an int32): the sweep runs in 32-bit arithmetic
+  // positions fit 31 bits (T is at most INT32_MAX - 16): the sweep runs in
+  // 32-bit arithmetic, from the chunk's start (past the end j0 would overflow)
   // Runs lie on the mask's 16-byte grid: rows that start off it (T not a
   // multiple of 16) have runs that start up to 15 positions early, and only
   // the runs across a row's ends are stored byte by byte (storing whole odd
   // rows by bytes took 32 rows of 9,001 positions from 4.5 to 9.4 us).
   const int32_t early = ALIGNED ? 0 : (int32_t)(((int64_t)seg * T) & 15);
   const int32_t c0 = (int32_t)chunk0 - early, c1 = ALIGNED || chunk1 == T ? (int32_t)chunk1 : (int32_t)chunk1 - early;
-  for (int32_t j0 = c0 + tid * kMapPerThread; j0 < c1; j0 += kMapThreads * kMapPerThread) {
+  for (int32_t o = tid * kMapPerThread; o < c1 - c0; o += kMapThreads * kMapPerThread) {
+    const int32_t j0 = c0 + o;
     const int32_t jl = j0 + kMapPerThread - 1;
     const bool whole = ALIGNED || (j0 >= 0 && jl < T);  // all 16 bytes are this row's
     // The run region by region: past the context, sink, recent window, a bin,

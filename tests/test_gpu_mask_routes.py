@@ -160,3 +160,27 @@ def test_map_regions(d, T, width):
         np.testing.assert_array_equal(qm.cpu().numpy(), want_q)
         np.testing.assert_array_equal(kv.cpu().numpy(), want)
         np.testing.assert_array_equal(ln.cpu().numpy(), want.sum(axis=2))
+
+
+@pytest.mark.parametrize("T", [(1 << 31) - 32, (1 << 31) - 17])
+def test_map_longest_contexts(d, T):
+    """The longest rows the map accepts, on and off the 16-byte grid: the last
+    sweep ends within 32 positions of the largest int32."""
+    S, R, W, D = 100, 1000, (1 << 17) - 1, 16384  # the last positions lie past the last bin
+    rng = np.random.default_rng(T & 0xFF)
+    pat = torch.from_numpy((rng.random((1, 2, D)) < 0.5).astype(np.uint8)).to(DEV)
+    lay = d.make_layout(1, 2, 2, 128, T, S, R, [W * i for i in range(D + 1)])
+    mask = torch.full((1, 2, T), 9, dtype=torch.uint8, device=DEV)
+    n = torch.zeros((1, 2), dtype=torch.int32, device=DEV)
+    d.dkv_map_pattern(lay, pat, mask, n)
+    for h in range(2):
+        kept = 0
+        for lo in range(0, T, 1 << 27):
+            j = torch.arange(lo, min(T, lo + (1 << 27)), dtype=torch.int64, device=DEV)
+            delta = T - 1 - j
+            u = (delta - R).clamp_(min=0)
+            want = pat[0, h][(u // W).clamp_(max=D - 1)].to(torch.bool) & (u < W * D)
+            want |= (j < S) | (delta < R)
+            assert torch.equal(mask[0, h, lo:lo + len(j)], want.to(torch.uint8)), (h, lo)
+            kept += int(want.sum())
+        assert int(n[0, h]) == kept
