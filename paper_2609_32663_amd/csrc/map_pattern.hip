@@ -58,12 +58,30 @@ __device__ __forceinline__ u32x4 mask_bytes(uint32_t keep) {
   return w;
 }
 
+typedef u32x4 __attribute__((aligned(1))) u32x4_bytes;  // 16 bytes anywhere
+
+// Stores the 16 mask bytes of positions [j0, j0 + 16), those that are the
+// row's; GRID: the address is a multiple of 16.
+template <bool GRID>
+__device__ __forceinline__ void store_run(uint8_t* row, int32_t j0, int32_t T, bool whole, u32x4 w) {
+  if (whole) {
+    if (GRID) *reinterpret_cast<u32x4*>(row + j0) = w;
+    else *reinterpret_cast<u32x4_bytes*>(row + j0) = w;
+  } else {
+#pragma unroll
+    for (int x = 0; x < kMapPerThread; ++x)
+      if (j0 + x >= 0 && j0 + x < T) row[j0 + x] = (uint8_t)(w[x >> 2] >> (8 * (x & 3)));
+  }
+}
+
 // ALIGNED: T is a multiple of 16, so every row starts on the 16-byte grid.
-template <bool ALIGNED>
+// HEADS: the per-query-head masks are written too.
+template <bool ALIGNED, bool HEADS>
 __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ int64_t red[kMapThreads / kWave + 1];
-  __shared__ uint16_t hbits[kMapThreads][kMapPerThread];  // per-position heads of mixed runs (for q_mask)
+  // heads that keep each position of a run of more than two regions
+  __shared__ uint16_t hbits[HEADS ? kMapPerThread : 1][kMapThreads];
 
   const int chunks = (int)map_chunks(p.T);
   const int seg = (int)(blockIdx.x / chunks);
@@ -130,9 +148,9 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
     // (Classifying runs across a region boundary position by position took
     // their waves 7 us, most of a small call.)
     uint32_t keep = 0;          // bit e: position j0 + e is kept
-    uint32_t rb = 0, rl = 0;    // heads of the first region and of the second
-    int32_t b = kMapPerThread;  // end of the first region
-    int regions = 0;
+    [[maybe_unused]] uint32_t rb = 0, rl = 0;    // heads of the first region and of the second
+    [[maybe_unused]] int32_t b = kMapPerThread;  // end of the first region
+    [[maybe_unused]] int regions = 0;
     int k = -1;  // bin of the previous region (D: the uncovered part), or none
     int32_t e = j0 < 0 ? -j0 : 0;
     while (e < kMapPerThread) {
@@ -163,55 +181,57 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
       }
       const int32_t end = n < kMapPerThread - e ? e + n : kMapPerThread;
       if (bits != 0u) keep |= (1u << end) - (1u << e);
-      if (regions == 0) {
-        rb = rl = bits;
-        b = end;
-      } else {
-        rl = bits;
+      if constexpr (HEADS) {
+        if (regions == 0) {
+          rb = rl = bits;
+          b = end;
+        } else if (regions == 1) {
+          rl = bits;
+        } else {
+          if (regions == 2)
+            for (int32_t x = 0; x < e; ++x) hbits[x][tid] = (uint16_t)(x < b ? rb : rl);
+          for (int32_t x = e; x < end; ++x) hbits[x][tid] = (uint16_t)bits;
+        }
+        ++regions;
       }
-      ++regions;
       e = end;
     }
-    if (whole) {
-      *reinterpret_cast<u32x4*>(kv_row + j0) = mask_bytes(keep);
-    } else {
-#pragma unroll 1
-      for (int x = 0; x < kMapPerThread; ++x)
-        if (j0 + x >= 0 && j0 + x < T) kv_row[j0 + x] = (keep >> x) & 1u;
-    }
-    if (p.q_mask != nullptr) {
-      const uint32_t head = (1u << b) - 1u;
-      if (regions > 2) {
-#pragma unroll 1
-        for (int x = 0; x < kMapPerThread; ++x) {
-          const int32_t j = j0 + x, delta = Tn - 1 - j;
-          uint32_t bits = 0;
-          if (j >= 0 && j < Tn) {
-            if (j < p.S || delta < p.R) {
-              bits = all_heads;
-            } else {
-              const int kx = find_bin(delta - p.R, edges, D, p.uniform_width);
-              if (kx >= 0) bits = qbits[kx];
-            }
-          }
-          hbits[tid][x] = (uint16_t)bits;
+    store_run<true>(kv_row, j0, T, whole, mask_bytes(keep));
+    if constexpr (HEADS) {
+      // The heads' masks from the regions.  A wave whose runs are all uniform
+      // has one word per head, one whose runs hold at most two regions a
+      // 16-bit keep mask; in the others every position's heads are picked
+      // apart in pairs.  (Classifying each position anew and building the
+      // masks bit by bit: 4 units of 8 groups of 8 heads at 131,072 with 512
+      // bins of 1 to 30 positions 72.5 us, now 18.6; at 131,071, whose rows are
+      // off the grid, 23.0 now, and 59.0 when every row was stored by bytes.)
+      uint8_t* q_row = p.q_mask + ((int64_t)unit * p.Hq + (int64_t)g * G) * T;
+      if (__builtin_amdgcn_ballot_w64(regions > 1) == 0) {
+        for (int h = 0; h < G; ++h, q_row += T) {
+          const uint32_t x = (rb >> h) & 1u ? 0x01010101u : 0u;
+          store_run<ALIGNED>(q_row, j0, T, whole, u32x4{x, x, x, x});
         }
-      }
-#pragma unroll 1
-      for (int h = 0; h < G; ++h) {
-        uint8_t* q_row = p.q_mask + ((int64_t)unit * p.Hq + (int64_t)g * G + h) * T;
-        uint32_t qk = ((rb >> h) & 1u ? head : 0u) | ((rl >> h) & 1u ? 0xFFFFu & ~head : 0u);
-        if (regions > 2) {
-          qk = 0;
-#pragma unroll 1
-          for (int x = 0; x < kMapPerThread; ++x) qk |= ((hbits[tid][x] >> h) & 1u) << x;
+      } else if (__builtin_amdgcn_ballot_w64(regions > 2) == 0) {
+        const uint32_t head = (1u << b) - 1u;
+        for (int h = 0; h < G; ++h, q_row += T) {
+          const uint32_t qk = ((rb >> h) & 1u ? head : 0u) | ((rl >> h) & 1u ? 0xFFFFu & ~head : 0u);
+          store_run<ALIGNED>(q_row, j0, T, whole, mask_bytes(qk));
         }
-        if (ALIGNED) {
-          *reinterpret_cast<u32x4*>(q_row + j0) = mask_bytes(qk);
-        } else {
-#pragma unroll 1
-          for (int x = 0; x < kMapPerThread; ++x)
-            if (j0 + x >= 0 && j0 + x < T) q_row[j0 + x] = (qk >> x) & 1u;
+      } else {
+        uint32_t pair[kMapPerThread / 2];
+#pragma unroll
+        for (int x = 0; x < kMapPerThread; x += 2) {
+          const uint32_t lo = regions > 2 ? hbits[x][tid] : (x < b ? rb : rl);
+          const uint32_t hi = regions > 2 ? hbits[x + 1][tid] : (x + 1 < b ? rb : rl);
+          pair[x / 2] = lo | hi << 16;
+        }
+        for (int h = 0; h < G; ++h, q_row += T) {
+          u32x4 w;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)  // bytes 0 and 2 of two pairs
+            w[q] = __builtin_amdgcn_perm((pair[2 * q + 1] >> h) & 0x00010001u, (pair[2 * q] >> h) & 0x00010001u,
+                                         0x06040200u);
+          store_run<ALIGNED>(q_row, j0, T, whole, w);
         }
       }
     }
@@ -227,10 +247,17 @@ hipError_t launch_map_pattern(const MapParams& p, int num_segments, hipStream_t 
   if (p.uniform_width == 0) lds += (size_t)(p.D + 1) * 4;
   const int64_t blocks = map_blocks(p.T, num_segments);
   if (blocks > 0) {
-    if ((p.T & 15) == 0)
-      hipLaunchKernelGGL(map_pattern_kernel<true>, dim3((uint32_t)blocks), dim3(kMapThreads), lds, stream, p);
-    else
-      hipLaunchKernelGGL(map_pattern_kernel<false>, dim3((uint32_t)blocks), dim3(kMapThreads), lds, stream, p);
+    auto map = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks), dim3(kMapThreads), lds, stream, p);
+    };
+    const bool aligned = (p.T & 15) == 0;
+    if (p.q_mask != nullptr) {
+      if (aligned) map(map_pattern_kernel<true, true>);
+      else map(map_pattern_kernel<false, true>);
+    } else {
+      if (aligned) map(map_pattern_kernel<true, false>);
+      else map(map_pattern_kernel<false, false>);
+    }
   }
   return hipGetLastError();
 }

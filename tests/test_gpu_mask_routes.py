@@ -184,3 +184,29 @@ def test_map_longest_contexts(d, T):
             assert torch.equal(mask[0, h, lo:lo + len(j)], want.to(torch.uint8)), (h, lo)
             kept += int(want.sum())
         assert int(n[0, h]) == kept
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("T,width", [(37, 1), (4099, 3), (4112, 17), (16400, 300), (2049, 5)])
+def test_map_heads(d, G, T, width):
+    """Every group size's masks per query head (the loads of the group's rows
+    come in batches), with and without the per-head output, runs of one, two
+    and more regions."""
+    rng = np.random.default_rng([G, T, width])
+    Hkv, S, R = 2, 5, 11
+    edges = [width * i for i in range(max(2, T // width - 20))]
+    pat = (rng.random((2, Hkv * G, len(edges) - 1)) < 0.3).astype(np.uint8)
+    lay = d.make_layout(2, Hkv * G, Hkv, 64, T, S, R, edges)
+    pt = torch.from_numpy(pat).to(DEV)
+    kv, kv2 = (torch.full((2, Hkv, T), 9, dtype=torch.uint8, device=DEV) for _ in range(2))
+    room = 64  # bytes behind the last head's row, which no store may touch
+    qm = torch.full((2 * Hkv * G * T + room,), 9, dtype=torch.uint8, device=DEV)
+    ln, ln2 = (torch.empty((2, Hkv), dtype=torch.int32, device=DEV) for _ in range(2))
+    d.dkv_map_pattern(lay, pt, kv, ln, q_mask=qm[:-room].view(2, Hkv * G, T))
+    d.dkv_map_pattern(lay, pt, kv2, ln2)
+    want_q, want, want_len = o.map_pattern(pat, T, S, R, edges, Hkv)
+    np.testing.assert_array_equal(qm[:-room].cpu().numpy().reshape(2, Hkv * G, T), want_q)
+    assert (qm[-room:] == 9).all()
+    for got, n in ((kv, ln), (kv2, ln2)):
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+        np.testing.assert_array_equal(n.cpu().numpy(), want_len)
