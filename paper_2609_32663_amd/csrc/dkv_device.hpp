@@ -155,17 +155,27 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
 // Bit h set when query head h of a group keeps bin k; prow is the group's
 // first pattern row (rows of D bytes).  Eight heads' loads are in flight at a
 // time (heads past G repeat the last row): one load per memory round trip
-// made eight heads cost six microseconds of a map call.
-__device__ __forceinline__ uint32_t group_bits(const uint8_t* prow, int D, int G, int k) {
+// made eight heads cost six microseconds of a map call.  Groups of at most
+// four, two and one head load four, two and one row instead of eight: one
+// head with 8,192 bins of 16 15.2 us a map call by one row, 19.6 by eight.
+template <int ROWS>
+__device__ __forceinline__ uint32_t group_bits_of(const uint8_t* prow, int D, int G, int k) {
   uint32_t bits = 0;
-  for (int h0 = 0; h0 < G; h0 += 8) {
-    uint32_t b[8];
+  for (int h0 = 0; h0 < G; h0 += ROWS) {
+    uint32_t b[ROWS];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) b[e] = prow[(int64_t)(h0 + e < G ? h0 + e : G - 1) * D + k];
+    for (int e = 0; e < ROWS; ++e) b[e] = prow[(int64_t)(h0 + e < G ? h0 + e : G - 1) * D + k];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) bits |= (h0 + e < G && b[e] != 0 ? 1u : 0u) << (h0 + e);
+    for (int e = 0; e < ROWS; ++e) bits |= (h0 + e < G && b[e] != 0 ? 1u : 0u) << (h0 + e);
   }
   return bits;
+}
+
+__device__ __forceinline__ uint32_t group_bits(const uint8_t* prow, int D, int G, int k) {
+  if (G == 1) return prow[k] != 0 ? 1u : 0u;
+  if (G == 2) return group_bits_of<2>(prow, D, G, k);
+  if (G <= 4) return group_bits_of<4>(prow, D, G, k);
+  return group_bits_of<8>(prow, D, G, k);
 }
 
 // The 16 mask bytes of positions [j0, j0 + 16) of mask row `row` (rows of T
