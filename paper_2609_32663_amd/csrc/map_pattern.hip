@@ -174,9 +174,10 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
             if (k < 0) k = D;
           }
           if (k < D) bits = qbits[k];
-          // the positions that stay at or above the region's lower edge
-          const int64_t lower = p.uniform_width > 0 ? (int64_t)p.uniform_width * k : edges[k];
-          n = u - lower < kMapPerThread ? (int32_t)(u - lower) + 1 : kMapPerThread;
+          // the positions that stay at or above the region's lower edge (edges
+          // fit 31 bits, and W * k is one)
+          const int32_t lower = p.uniform_width > 0 ? p.uniform_width * k : edges[k];
+          n = u - lower + 1;
         }
       }
       const int32_t end = n < kMapPerThread - e ? e + n : kMapPerThread;
