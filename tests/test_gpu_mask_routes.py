@@ -187,7 +187,7 @@ def test_map_longest_contexts(d, T):
 
 
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
-@pytest.mark.parametrize("T,width", [(37, 1), (4099, 3), (4112, 17), (16400, 300), (2049, 5)])
+@pytest.mark.parametrize("T,width", [(37, 1), (4099, 2), (4099, 3), (4112, 1), (4112, 17), (16400, 300), (2049, 5)])
 def test_map_heads(d, G, T, width):
     """Every group size's masks per query head (the loads of the group's rows
     come in batches), with and without the per-head output, runs of one, two
