@@ -273,7 +273,7 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t stream) {
     if (!whole) hipLaunchKernelGGL(compact_list_kernel, grid, dim3(kThreads), 0, stream, p);
     const int rows = copy_rows(p.T, p.row_bytes);
     auto copy = [&](auto kernel) {  // a K and a V workgroup per chunk
-      hipLaunchKernelGGL(kernel, dim3((uint32_t)copy_workgroups(p.T, rows), p.nseg), dim3(kThreads), 0, stream, p);
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)copy_grid(p.T, rows, p.nseg), p.nseg), dim3(kThreads), 0, stream, p);
     };
     switch (p.row_bytes) {
       case 128: copy(compact_copy_kernel<8, 64>); break;

@@ -31,6 +31,7 @@
 
 #include "dkv_bins.hpp"
 #include "dkv_device.hpp"
+#include "dkv_launch.hpp"
 
 namespace dkv {
 
@@ -257,8 +258,9 @@ hipError_t launch_compact_bins(const BinsParams& p, hipStream_t stream) {
   hipLaunchKernelGGL(bins_plan_kernel, dim3(p.nseg), dim3(kPlanThreads), (size_t)p.D, stream, p);
   hipLaunchKernelGGL(bins_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, p);
   if (p.nchunks > 0) {
-    const dim3 grid(2 * p.nchunks, p.nseg);  // a K and a V workgroup per chunk
-    const dim3 half(2 * ((p.nchunks + 1) / 2), p.nseg);
+    // a K and a V workgroup per chunk
+    const dim3 grid((uint32_t)copy_grid(p.T, kBinsChunkRows, p.nseg), p.nseg);
+    const dim3 half((uint32_t)copy_grid(p.T, 2 * kBinsChunkRows, p.nseg), p.nseg);
     switch (p.row_bytes) {
       case 128: hipLaunchKernelGGL((bins_copy_kernel<8, 2>), half, dim3(kThreads), 0, stream, p); break;
       case 256: hipLaunchKernelGGL((bins_copy_kernel<16, 1>), grid, dim3(kThreads), 0, stream, p); break;

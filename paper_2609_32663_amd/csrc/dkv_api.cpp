@@ -233,8 +233,7 @@ dkv_status compact_bins(const dkv_layout* layout, const int32_t* unit_len, dkv_d
   const int64_t nseg = (int64_t)L.num_units * L.num_kv_heads;
   if (nseg > 65535 || nseg * ((int64_t)L.num_bins + 3) > (int64_t(1) << 27)) return DKV_ERR_UNSUPPORTED;
   // as for dkv_compact: the copy dispatch must hold fewer than 2^32 work-items
-  if (2 * (((int64_t)L.context_len + dkv::kBinsChunkRows - 1) / dkv::kBinsChunkRows) * 256 > (int64_t)UINT32_MAX)
-    return DKV_ERR_UNSUPPORTED;
+  if (!dkv::copy_dispatch_fits(L.context_len, dkv::kBinsChunkRows)) return DKV_ERR_UNSUPPORTED;
   if (nseg == 0) return DKV_OK;
   if (k == nullptr || v == nullptr || pattern == nullptr || k_out == nullptr || v_out == nullptr ||
       seg_off == nullptr || seg_len == nullptr)

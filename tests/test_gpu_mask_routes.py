@@ -210,3 +210,43 @@ def test_map_heads(d, G, T, width):
     for got, n in ((kv, ln), (kv2, ln2)):
         np.testing.assert_array_equal(got.cpu().numpy(), want)
         np.testing.assert_array_equal(n.cpu().numpy(), want_len)
+
+
+@pytest.mark.parametrize("dim,dtype,T", [(64, torch.bfloat16, 1024), (64, torch.bfloat16, 4096), (64, torch.bfloat16, 4097),
+                                         (128, torch.bfloat16, 128), (128, torch.bfloat16, 2048), (128, torch.float32, 64),
+                                         (128, torch.float32, 1024), (128, torch.float32, 100)])
+@pytest.mark.parametrize("nseg", [63, 64, 65])
+def test_pack_grids_of_many_segments(d, dim, dtype, T, nseg):
+    """Either side of the rule that gives every segment one idle workgroup more
+    (64 segments, 128 workgroups a segment, a multiple of four), with full,
+    empty and partly kept segments: the mask pack and the block gather of the
+    same rows agree with each other and with the rows picked by the mask."""
+    rng = np.random.default_rng([dim, T, nseg])
+    edges = [0, T // 4, T // 2, T - T // 4, T]
+    pat = (rng.random((nseg, 1, 4)) < 0.5).astype(np.uint8)
+    pat[0], pat[-1] = 1, 0
+    lay = d.make_layout(nseg, 1, 1, dim, T, 0, 0, edges)
+    k, v = (torch.randn((nseg, 1, T, dim), device=DEV).to(dtype) for _ in range(2))
+    pt = torch.from_numpy(pat).to(DEV)
+    mask = torch.empty((nseg, 1, T), dtype=torch.uint8, device=DEV)
+    kl = torch.empty((nseg, 1), dtype=torch.int32, device=DEV)
+    d.dkv_map_pattern(lay, pt, mask, kl)
+    rows = int(kl.sum()) + 3 * nseg
+    keep = mask[:, 0].bool()
+    lens = kl[:, 0].long()
+    off = torch.cumsum(lens + 3, 0) - (lens + 3)
+    at = torch.cat([off[s] + torch.arange(int(lens[s]), device=DEV) for s in range(nseg)])
+    for bins in (False, True):
+        ko, vo = (torch.full((rows, dim), 7.0, dtype=dtype, device=DEV) for _ in range(2))
+        so, sl = torch.empty(nseg, dtype=torch.int64, device=DEV), torch.empty(nseg, dtype=torch.int32, device=DEV)
+        if bins:
+            ws = torch.empty(max(16, d.dkv_compact_bins_workspace_bytes(lay)), dtype=torch.uint8, device=DEV)
+            d.dkv_compact_bins(lay, k, v, pt, 3, ko, vo, so, sl, ws)
+        else:
+            ws = torch.empty(d.dkv_compact_workspace_bytes(lay), dtype=torch.uint8, device=DEV)
+            d.dkv_compact(lay, k, v, mask, 3, ko, vo, so, sl, ws)
+        assert torch.equal(so, off) and torch.equal(sl.long(), lens)
+        for got, src in ((ko, k), (vo, v)):
+            want = torch.full((rows, dim), 7.0, dtype=dtype, device=DEV)
+            want[at] = src[:, 0][keep]
+            assert torch.equal(got, want)
