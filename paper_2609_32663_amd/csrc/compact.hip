@@ -16,8 +16,8 @@
 //           entry.
 // Where one workgroup per segment can walk the whole mask row
 // (rank_whole_segments), compact_rank_kernel takes the place of count and
-// list: the mask is read once (32 segments of 9,001 positions: count, scan and
-// list 12.3 us, rank and scan 8.4).
+// list: the mask is read once (the pack of 32 segments of 9,001 positions of 256
+// bytes 28.4 us with count and list, 25.6 with rank).
 // The copy works on the output side because short workgroups copy fastest on
 // this part and every copy workgroup then has whole rows to move: on the
 // Llama-3.1-8B-shaped 128K stack (35% kept) the pack takes 1.91-1.97 ms this
@@ -127,57 +127,41 @@ __global__ __launch_bounds__(kThreads) void compact_list_kernel(CompactParams p)
 // One workgroup per segment lists the segment's retained positions (a
 // position's rank counts from its own segment's start, so no other segment
 // is needed) and leaves the segment's count in tile_cnt[seg]: the mask is
-// read once and the count pass falls away.  Runs of 16 positions are written
-// by waves: a wave whose runs are all kept writes its 1,024 positions
-// directly; other waves order theirs in LDS first, so that stores are
-// coalesced.
-__global__ __launch_bounds__(kSweepThreads) void compact_rank_kernel(CompactParams p) {
-  __shared__ int32_t tmp[kSweeps * kSweepThreads / kWave];
-  __shared__ int32_t pos[kSweepThreads / kWave][kWave * 16];
+// read once and the count pass falls away.  A wave whose positions are all kept
+// writes its 1,024 directly; the others order theirs in LDS first, so that
+// stores are coalesced.
+constexpr int kRankThreads = 1024;
+constexpr int kRankPositions = kRankThreads * kPerThread;
+
+__global__ __launch_bounds__(kRankThreads) void compact_rank_kernel(CompactParams p) {
+  constexpr int kWaves = kRankThreads / kWave;
+  __shared__ int32_t sums[kWaves];
+  __shared__ int32_t pos[kWaves][kWave * kPerThread];
   const int seg = blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  int32_t* list = p.list + (int64_t)seg * p.T;
-  int32_t first = 0;  // positions kept in the panels before
-  for (int64_t base = 0; base < p.T; base += kPanelPositions) {
-    uint32_t keep[kSweeps];
-    panel_bits(p.mask, seg, p.nseg, base, p.T, keep);
-    int rank[kSweeps];
+  const uint32_t keep = nonzero_byte_bits(load_mask16(p.mask, seg, p.nseg, (int64_t)threadIdx.x * kPerThread, p.T));
+  const int inc = (int)wave_inclusive_sum((uint32_t)__popc(keep));
+  const int n = __builtin_amdgcn_readlane(inc, kWave - 1);  // kept positions of the wave
+  if (lane == 0) sums[wave] = n;
+  __syncthreads();
+  const int upto = (int)wave_inclusive_sum(lane < kWaves ? (uint32_t)sums[lane] : 0u);
+  const int first = __builtin_amdgcn_readlane(upto, wave) - n;
+  if (threadIdx.x == 0) p.tile_cnt[seg] = __builtin_amdgcn_readlane(upto, kWaves - 1);
+  if (n == 0) return;
+  int32_t* dst = p.list + (int64_t)seg * p.T + first;
+  const int32_t j0 = wave * (kWave * kPerThread);
+  if (n == kWave * kPerThread) {
 #pragma unroll
-    for (int c = 0; c < kSweeps; ++c) rank[c] = __popc(keep[c]);
-    const int kept = sweep_ranks(rank, tmp);
-    for (int c = 0; c < kSweeps; ++c) {
-      if (base + c * kSweepPositions >= p.T) break;
-      uint32_t kb = 0;
-      int rk = 0;
-#pragma unroll
-      for (int i = 0; i < kSweeps; ++i)
-        if (i == c) {
-          kb = keep[i];
-          rk = rank[i];
-        }
-      if (__builtin_amdgcn_ballot_w64(kb != 0u) == 0) continue;
-      const int r0 = __builtin_amdgcn_readfirstlane(rk);  // the wave's first rank
-      const int32_t j0 = (int32_t)(base + c * kSweepPositions + wave * (kWave * 16));
-      int32_t* dst = list + first + r0;
-      if (__builtin_amdgcn_ballot_w64(kb != 0xFFFFu) == 0) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) dst[e * kWave + lane] = j0 + e * kWave + lane;
-        continue;
-      }
-      int at = rk - r0;
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (kb & (1u << e)) pos[wave][at++] = j0 + lane * 16 + e;
-      const int n = __builtin_amdgcn_readlane(at, kWave - 1);
-      wave_lds_fence();
-      for (int i = lane; i < n; i += kWave) dst[i] = pos[wave][i];
-      wave_lds_fence();
-    }
-    first += kept;
-    __syncthreads();  // tmp is free again
+    for (int e = 0; e < kPerThread; ++e) dst[e * kWave + lane] = j0 + e * kWave + lane;
+    return;
   }
-  if (threadIdx.x == 0) p.tile_cnt[seg] = first;
+  int at = inc - __popc(keep);
+#pragma unroll
+  for (int e = 0; e < kPerThread; ++e)
+    if (keep & (1u << e)) pos[wave][at++] = j0 + lane * kPerThread + e;
+  wave_lds_fence();
+  for (int i = lane; i < n; i += kWave) dst[i] = pos[wave][i];
 }
 
 template <int LPR, int ROWS>
@@ -243,15 +227,16 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p) {
 
 }  // namespace
 
-// A workgroup walks its row in panels one after the other, so whole rows pay
-// when they are short or when the segments fill the chip: one segment per 4096
-// positions of a row.  Map and page selection, whole / tiles, us: 8 segments
-// of 32,768 14.8 / 15.2, of 131,072 15.8 / 14.8, of 262,144 23.1 / 15.2; 32 of
-// 131,072 17.3 / 17.5, of 262,144 26.8 / 22.8; 64 of 262,144 27.9 / 29.0, of
-// 524,288 47.0 / 43.4; 256 of 131,072 25.8 / 49.7.
-bool rank_whole_segments(int32_t T, int64_t nseg) {
-  return T <= 32768 || (T <= 4 * kPanelPositions && T <= nseg * kCompactTile);
-}
+// Whether one workgroup per segment ranks its whole mask row (16 positions a
+// thread), or the workgroups take 4096-position tiles in two passes.  A round
+// of whole rows takes as long for a few positions as for all, so tiles are
+// ahead again for thousands of short segments, and longer rows, which a
+// workgroup walked in steps, were so throughout.  The whole pack, whole /
+// tiles, us (256-byte rows, 35% kept in runs of 64): 1 segment of 256
+// positions 8.9 / 11.2, of 16,384 10.2 / 12.4; 256 of 256 13.6 / 16.3, of
+// 16,384 254 / 255; 1,024 of 100 18.4 / 21.0, of 1,024 70.1 / 71.5; 4,096 of
+// 100 49.0 / 48.1, of 1,024 270.6 / 268.1; 16,384 of 256 329 / 311.
+static bool rank_whole_segments(int32_t T, int64_t nseg) { return T <= kRankPositions && nseg <= 1024; }
 
 size_t compact_workspace_bytes(int64_t nseg, int64_t T) {
   const int64_t ntiles = (T + kCompactTile - 1) / kCompactTile;

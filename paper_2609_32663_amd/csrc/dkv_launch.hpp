@@ -66,10 +66,6 @@ constexpr int copy_rows(int64_t T, int row_bytes) {
   return copy_dispatch_fits(T, rows) ? rows : kCopyRows;
 }
 
-// Whether one workgroup per segment walks its whole mask row, or the
-// workgroups take 4096-position tiles.
-bool rank_whole_segments(int32_t T, int64_t nseg);
-
 struct CompactParams {
   const uint8_t* mask;     // [nseg][T]
   const void* k;           // [nseg][T][d]

@@ -11,7 +11,7 @@
 //
 // A run starts at a kept position whose predecessor is not kept or that opens
 // a page.  Short contexts, and longer ones with enough segments
-// (rank_whole_segments), take one workgroup per segment and one pass over the
+// (select_whole_segments), take one workgroup per segment and one pass over the
 // mask (page_select_kernel): 256 segments of 131,072 positions, map included,
 // took 49.7 us in the two passes below and take 25.8 (14.0 for the selection
 // alone, against 39).  With fewer or longer segments one workgroup each would
@@ -319,6 +319,12 @@ __global__ __launch_bounds__(kThreads) void page_empty_kernel(PageSelectParams p
 
 }  // namespace
 
+// Whether one workgroup per segment walks its whole mask row (in panels one
+// after the other), or the workgroups take 4096-position tiles in two passes.
+bool select_whole_segments(int32_t T, int64_t nseg) {
+  return T <= 32768 || (T <= 4 * kPanelPositions && T <= nseg * kCompactTile);
+}
+
 size_t page_select_workspace_bytes(int64_t nseg, int64_t T) {
   const int64_t ntiles = (T + kCompactTile - 1) / kCompactTile;
   return (size_t)((ntiles > kSumTiles ? 3 : 2) * nseg * ntiles) * sizeof(int32_t);
@@ -326,7 +332,7 @@ size_t page_select_workspace_bytes(int64_t nseg, int64_t T) {
 
 hipError_t launch_page_select(PageSelectParams p, hipStream_t stream) {
   if (p.nseg == 0) return hipSuccess;
-  if (p.ntiles > 0 && rank_whole_segments(p.T, p.nseg)) {
+  if (p.ntiles > 0 && select_whole_segments(p.T, p.nseg)) {
     hipLaunchKernelGGL(page_select_kernel, dim3(p.nseg), dim3(kSweepThreads), 0, stream, p);
   } else if (p.ntiles > 0) {
     // workspace: tile counts, kept positions, and for long contexts each tile's first entry

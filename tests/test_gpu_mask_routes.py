@@ -67,7 +67,10 @@ def test_page_select_panels(d, nseg, T, page_rows, cap):
 
 @pytest.mark.parametrize("nseg,T,dim,dtype", [(64, 131085, 64, torch.bfloat16), (2, 131080, 64, torch.float32),
                                               (2, 32768, 128, torch.float32), (3, 32769, 128, torch.bfloat16),
-                                              (33, 133333, 64, torch.bfloat16), (3, 9001, 128, torch.bfloat16)])
+                                              (33, 133333, 64, torch.bfloat16), (3, 9001, 128, torch.bfloat16),
+                                              (3, 16383, 64, torch.bfloat16), (3, 16384, 64, torch.bfloat16),
+                                              (3, 16385, 64, torch.bfloat16), (1024, 1023, 64, torch.bfloat16),
+                                              (1025, 1023, 64, torch.bfloat16), (1024, 1040, 64, torch.bfloat16)])
 def test_compact_panels(d, nseg, T, dim, dtype):
     mask = _mask(nseg, T, T)
     k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
