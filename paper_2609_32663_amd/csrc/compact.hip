@@ -140,28 +140,36 @@ __global__ __launch_bounds__(kRankThreads) void compact_rank_kernel(CompactParam
   const int seg = blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint32_t keep = nonzero_byte_bits(load_mask16(p.mask, seg, p.nseg, (int64_t)threadIdx.x * kPerThread, p.T));
-  const int inc = (int)wave_inclusive_sum((uint32_t)__popc(keep));
-  const int n = __builtin_amdgcn_readlane(inc, kWave - 1);  // kept positions of the wave
-  if (lane == 0) sums[wave] = n;
-  __syncthreads();
-  const int upto = (int)wave_inclusive_sum(lane < kWaves ? (uint32_t)sums[lane] : 0u);
-  const int first = __builtin_amdgcn_readlane(upto, wave) - n;
-  if (threadIdx.x == 0) p.tile_cnt[seg] = __builtin_amdgcn_readlane(upto, kWaves - 1);
-  if (n == 0) return;
-  int32_t* dst = p.list + (int64_t)seg * p.T + first;
-  const int32_t j0 = wave * (kWave * kPerThread);
-  if (n == kWave * kPerThread) {
+  int32_t* list = p.list + (int64_t)seg * p.T;
+  int first = 0;  // positions kept in the steps before
+  u32x4 w = load_mask16(p.mask, seg, p.nseg, (int64_t)threadIdx.x * kPerThread, p.T);
+  for (int64_t base = 0; base < p.T; base += kRankPositions) {
+    const uint32_t keep = nonzero_byte_bits(w);
+    // the next step's mask is on its way meanwhile
+    w = load_mask16(p.mask, seg, p.nseg, base + kRankPositions + (int64_t)threadIdx.x * kPerThread, p.T);
+    const int inc = (int)wave_inclusive_sum((uint32_t)__popc(keep));
+    const int n = __builtin_amdgcn_readlane(inc, kWave - 1);  // kept positions of the wave
+    if (lane == 0) sums[wave] = n;
+    __syncthreads();
+    const int upto = (int)wave_inclusive_sum(lane < kWaves ? (uint32_t)sums[lane] : 0u);
+    int32_t* dst = list + first + __builtin_amdgcn_readlane(upto, wave) - n;
+    first += __builtin_amdgcn_readlane(upto, kWaves - 1);
+    const int32_t j0 = (int32_t)base + wave * (kWave * kPerThread);
+    if (n == kWave * kPerThread) {
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) dst[e * kWave + lane] = j0 + e * kWave + lane;
-    return;
+      for (int e = 0; e < kPerThread; ++e) dst[e * kWave + lane] = j0 + e * kWave + lane;
+    } else if (n > 0) {
+      int at = inc - __popc(keep);
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e)
+        if (keep & (1u << e)) pos[wave][at++] = j0 + lane * kPerThread + e;
+      wave_lds_fence();
+      for (int i = lane; i < n; i += kWave) dst[i] = pos[wave][i];
+      wave_lds_fence();
+    }
+    __syncthreads();  // sums is free again
   }
-  int at = inc - __popc(keep);
-#pragma unroll
-  for (int e = 0; e < kPerThread; ++e)
-    if (keep & (1u << e)) pos[wave][at++] = j0 + lane * kPerThread + e;
-  wave_lds_fence();
-  for (int i = lane; i < n; i += kWave) dst[i] = pos[wave][i];
+  if (threadIdx.x == 0) p.tile_cnt[seg] = first;
 }
 
 template <int LPR, int ROWS>
@@ -227,16 +235,19 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendParams p) {
 
 }  // namespace
 
-// Whether one workgroup per segment ranks its whole mask row (16 positions a
-// thread), or the workgroups take 4096-position tiles in two passes.  A round
-// of whole rows takes as long for a few positions as for all, so tiles are
-// ahead again for thousands of short segments, and longer rows, which a
-// workgroup walked in steps, were so throughout.  The whole pack, whole /
-// tiles, us (256-byte rows, 35% kept in runs of 64): 1 segment of 256
-// positions 8.9 / 11.2, of 16,384 10.2 / 12.4; 256 of 256 13.6 / 16.3, of
-// 16,384 254 / 255; 1,024 of 100 18.4 / 21.0, of 1,024 70.1 / 71.5; 4,096 of
-// 100 49.0 / 48.1, of 1,024 270.6 / 268.1; 16,384 of 256 329 / 311.
-static bool rank_whole_segments(int32_t T, int64_t nseg) { return T <= kRankPositions && nseg <= 1024; }
+// Whether one workgroup per segment ranks its whole mask row, 16,384 positions
+// at a step, or the workgroups take 4096-position tiles in two passes.  A round
+// of whole rows takes as long for a few positions as for a step, so tiles are
+// ahead for thousands of short segments, and for long rows that too few
+// workgroups walk step by step.  The whole pack, whole / tiles, us (256-byte
+// rows, 35% kept in runs of 64): 1 segment of 256 positions 8.9 / 11.2, of
+// 32,768 13.3 / 13.5, of 65,536 19.7 / 16.0; 32 of 32,768 71.0 / 71.5, of
+// 131,072 268 / 258; 128 of 131,072, 128-byte rows, 522 / 522; 256 of 16,384
+// 254 / 255; 1,024 of 1,024 70.1 / 71.5; 4,096 of 100 49.0 / 48.1, of 1,024
+// 270.6 / 268.1, of 4,096, 128-byte rows, 518 / 524; 16,384 of 256 329 / 311.
+static bool rank_whole_segments(int32_t T, int64_t nseg) {
+  return T <= 8 * kRankPositions && (nseg >= 128 || T <= 2 * kRankPositions) && (nseg <= 1024 || T >= kCompactTile);
+}
 
 size_t compact_workspace_bytes(int64_t nseg, int64_t T) {
   const int64_t ntiles = (T + kCompactTile - 1) / kCompactTile;

@@ -70,7 +70,10 @@ def test_page_select_panels(d, nseg, T, page_rows, cap):
                                               (33, 133333, 64, torch.bfloat16), (3, 9001, 128, torch.bfloat16),
                                               (3, 16383, 64, torch.bfloat16), (3, 16384, 64, torch.bfloat16),
                                               (3, 16385, 64, torch.bfloat16), (1024, 1023, 64, torch.bfloat16),
-                                              (1025, 1023, 64, torch.bfloat16), (1024, 1040, 64, torch.bfloat16)])
+                                              (1025, 1023, 64, torch.bfloat16), (1024, 1040, 64, torch.bfloat16),
+                                              (127, 33000, 64, torch.bfloat16), (128, 33001, 64, torch.bfloat16),
+                                              (128, 32784, 64, torch.bfloat16), (1025, 4096, 64, torch.bfloat16),
+                                              (1025, 4095, 64, torch.bfloat16), (128, 131072, 64, torch.bfloat16)])
 def test_compact_panels(d, nseg, T, dim, dtype):
     mask = _mask(nseg, T, T)
     k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
