@@ -321,8 +321,24 @@ __global__ __launch_bounds__(kThreads) void page_empty_kernel(PageSelectParams p
 
 // Whether one workgroup per segment walks its whole mask row (in panels one
 // after the other), or the workgroups take 4096-position tiles in two passes.
-bool select_whole_segments(int32_t T, int64_t nseg) {
-  return T <= 32768 || (T <= 4 * kPanelPositions && T <= nseg * kCompactTile);
+// A workgroup fills its CU, so the segments take rounds of 256: past the first
+// round short rows lose (a round costs 6 us), and a few long rows leave the
+// chip idle.  Rows of very many runs spend their time writing entries, which
+// the tiles spread wider: the caller's bound on the entries tells (a mapped
+// mask has one per page and bin, far below T / 4).  The selection alone, whole
+// / tiles, us (128-row pages, 35% kept in runs of 64): 16 segments of 65,536
+// 10.3 / 9.9; 64 of 131,072 12.0 / 15.1, of 262,144 19.9 / 21.5; 128 of 524,288
+// 43 / 64; 256 of 131,072 14.1 / 39; 512 of 1,024 15.6 / 9.8, of 24,576 16.4 /
+// 18.2; 1,024 of 16,384 29 / 22, of 32,768 31 / 39; 4,096 of 1,024 100 / 21, of
+// 32,768 117 / 130.  Single positions (an entry per 4.4): 16 of 32,768 17.8 /
+// 12.0, 256 of 131,072 106 / 87.
+bool select_whole_segments(const PageSelectParams& p) {
+  const int64_t T = p.T, nseg = p.nseg;
+  if (T > 4 * kPanelPositions) return false;
+  if (nseg <= 256 && T <= 10240) return true;
+  if (p.max_entries > T / 4) return false;
+  if (nseg <= 256) return T <= 32768 || (nseg >= 64 && T <= nseg * kCompactTile);
+  return T >= (nseg <= 512 ? 24000 : 32768);
 }
 
 size_t page_select_workspace_bytes(int64_t nseg, int64_t T) {
@@ -332,7 +348,7 @@ size_t page_select_workspace_bytes(int64_t nseg, int64_t T) {
 
 hipError_t launch_page_select(PageSelectParams p, hipStream_t stream) {
   if (p.nseg == 0) return hipSuccess;
-  if (p.ntiles > 0 && select_whole_segments(p.T, p.nseg)) {
+  if (p.ntiles > 0 && select_whole_segments(p)) {
     hipLaunchKernelGGL(page_select_kernel, dim3(p.nseg), dim3(kSweepThreads), 0, stream, p);
   } else if (p.ntiles > 0) {
     // workspace: tile counts, kept positions, and for long contexts each tile's first entry

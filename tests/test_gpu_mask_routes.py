@@ -45,7 +45,11 @@ def _select(d, mask, page_rows, cap, pages, bound):
 
 @pytest.mark.parametrize("nseg,T,page_rows,cap", [(64, 131072, 32, 37), (64, 131077, 32, 0), (72, 290001, 128, 300),
                                                   (40, 163840, 64, 1), (40, 163841, 64, 1), (4, 32768, 32, 5),
-                                                  (4, 32769, 32, 5), (3, 17, 32, 40)])
+                                                  (4, 32769, 32, 5), (3, 17, 32, 40), (256, 10240, 64, 3),
+                                                  (256, 10241, 64, 3), (257, 10240, 64, 3), (257, 32768, 128, 9),
+                                                  (257, 32767, 128, 9), (512, 24000, 128, 9), (512, 23999, 128, 9),
+                                                  (513, 24000, 128, 9), (64, 262144, 1024, 7), (64, 262145, 1024, 7),
+                                                  (63, 131072, 1024, 7)])
 def test_page_select_panels(d, nseg, T, page_rows, cap):
     """One panel, two and three, and either side of the rule that sends a call
     to the tile passes, against the oracle."""
@@ -63,6 +67,29 @@ def test_page_select_panels(d, nseg, T, page_rows, cap):
         assert (ent[s, len(e):] == -5).all()
         assert ln[s] == want["seg_len"][i]
         np.testing.assert_array_equal(used[s], want["page_used"][i])
+
+
+@pytest.mark.parametrize("nseg,T", [(5, 16384), (5, 20001), (130, 131072), (300, 33333)])
+def test_page_select_bound_rule(d, nseg, T):
+    """The caller's bound on the entries chooses between the whole-row kernel
+    and the tile passes: a quarter of the positions, one more, and bounds below
+    the entries there are (the first ones written, the true number reported)
+    give the same outputs."""
+    mask = _mask(nseg, T, T)
+    pages = -(-(T + 5) // 64)
+    first = None
+    for bound in (T // 4, T // 4 + 1, T // 2, 200):
+        _, ent, n, ln, used = _select(d, mask, 64, 5, pages, bound)
+        if first is None:
+            first = (ent, n, ln, used)
+            assert n.max() > 200
+        keep = min(bound, T // 4)
+        for s in range(nseg):
+            m = min(int(n[s]), keep)
+            np.testing.assert_array_equal(ent[s, :m], first[0][s, :m])
+            assert (ent[s, min(int(n[s]), bound):] == -5).all()
+        for a, b in zip((n, ln, used), first[1:]):
+            np.testing.assert_array_equal(a, b)
 
 
 @pytest.mark.parametrize("nseg,T,dim,dtype", [(64, 131085, 64, torch.bfloat16), (2, 131080, 64, torch.float32),
