@@ -38,10 +38,14 @@ namespace dkv {
 namespace {
 
 constexpr int kThreads = 256;
-// One workgroup plans a segment; its chunk heads are a binary search each, so
-// more threads shorten it (64 segments of 1,013 bins and up to 2,800 chunks:
-// 14.7 us with 256 threads, 8.2 with 1,024).
-constexpr int kPlanThreads = 1024;
+// One workgroup plans a segment.  Its ranges and its chunk heads (a binary
+// search each) go over the threads, so many of either want 1,024 (64 segments of
+// 1,013 bins and up to 2,800 chunks: 14.7 us with 256 threads, 8.2 with 1,024);
+// a few start and end sooner with 256 (the whole pack of 8 segments of 14 bins
+// and 1,000 positions 12.2 us with 1,024 and 11.3 with 256; of 4,096 such
+// segments 205 and 184).
+constexpr int kPlanWide = 1024, kPlanNarrow = 256;
+inline bool plan_wide(const BinsParams& p) { return p.D > 512 || p.nchunks >= 1024; }
 constexpr int kScanThreads = 1024;
 constexpr int kMaxUnroll = 8;  // rows per lane group in flight, at most
 
@@ -79,6 +83,7 @@ __device__ __forceinline__ void range_of(const BinsParams& p, int64_t T, int i, 
 // heads cooperatively (16 KiB); segments with more fall back to the serial fill.
 constexpr int kPlanTable = 4096;
 
+template <int kPlanThreads>
 __global__ __launch_bounds__(kPlanThreads) void bins_plan_kernel(BinsParams p) {
   __shared__ int64_t red[kPlanThreads / kWave + 1];
   __shared__ int32_t tbl[kPlanTable];
@@ -255,7 +260,10 @@ size_t bins_workspace_bytes(int64_t nseg, int32_t D, int32_t T) {
 }
 
 hipError_t launch_compact_bins(const BinsParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL(bins_plan_kernel, dim3(p.nseg), dim3(kPlanThreads), (size_t)p.D, stream, p);
+  if (plan_wide(p))
+    hipLaunchKernelGGL(bins_plan_kernel<kPlanWide>, dim3(p.nseg), dim3(kPlanWide), (size_t)p.D, stream, p);
+  else
+    hipLaunchKernelGGL(bins_plan_kernel<kPlanNarrow>, dim3(p.nseg), dim3(kPlanNarrow), (size_t)p.D, stream, p);
   hipLaunchKernelGGL(bins_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, p);
   if (p.nchunks > 0) {
     // a K and a V workgroup per chunk

@@ -247,3 +247,15 @@ def test_compact_bins_many_segments(d):
     k, v, pattern = _inputs(rng, N, Hq, Hkv, dim, T, torch.bfloat16, 3, 0.4)
     res, *_ = _both(d, lay, pattern, k, v, 2)
     _assert_same(res)
+
+
+@pytest.mark.parametrize("D,T", [(512, 2000), (513, 2000), (40, 32736), (40, 32768), (600, 40000)])
+def test_bins_plan_threads(d, D, T):
+    """Either side of the rule that plans a segment with 256 or 1,024 threads
+    (more than 512 bins, 1,024 chunk heads)."""
+    rng = np.random.default_rng([D, T])
+    w = max(1, T // D)
+    lay = d.make_layout(2, 4, 2, 64, T, 3, 17, [w * i for i in range(D + 1)])
+    pattern = torch.from_numpy((rng.random((2, 4, D)) < 0.3).astype(np.uint8)).to(DEV)
+    k, v = (torch.randn((2, 2, T, 64), device=DEV).to(torch.bfloat16) for _ in range(2))
+    _assert_same(_both(d, lay, pattern, k, v, 5)[0])
