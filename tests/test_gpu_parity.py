@@ -336,13 +336,14 @@ def test_compact_out_rows_exact_edge(d, short):
     assert (src[last_lo:] == -7).all()
 
 
-def test_truncated_compaction_is_safe_downstream(d):
+@pytest.mark.parametrize("n_q", [4, 140], ids=["short_block", "long_block"])
+def test_truncated_compaction_is_safe_downstream(d, n_q):
     """A pack that does not fit out_rows: segments that fit are packed whole,
     the others get seg_len -1 and an offset clamped to out_rows; append,
     decode (plain and fused) and query attention then write nothing at or
     past out_rows, skip those segments and give zeros for them."""
     rng = np.random.default_rng(206)
-    B, Hkv, G, T, dim, cap, n_q = 1, 3, 2, 2000, 128, 8, 4
+    B, Hkv, G, T, dim, cap = 1, 3, 2, 2000, 128, n_q + 4
     Hq = Hkv * G
     mask = (rng.uniform(size=(B, Hkv, T)) < 0.5).astype(np.uint8)
     lens = mask.reshape(-1, T).sum(-1).astype(np.int64)
@@ -397,7 +398,8 @@ def test_truncated_compaction_is_safe_downstream(d):
     assert (got[:, G:] == 0).all()
     np.testing.assert_array_equal(bits(k_c)[n0:n0 + 3], bits(kn)[0])
 
-    # query attention of a 4-token block appended after the three tokens
+    # query attention of a block appended after the three tokens (8 and 280
+    # query rows per segment: a kernel each)
     kb = _rand_kv(rng, (Hkv, n_q, dim), torch.bfloat16)
     vb = _rand_kv(rng, (Hkv, n_q, dim), torch.bfloat16)
     d.dkv_append(kb, vb, 3, cap, k_c, v_c, seg_off, seg_len)

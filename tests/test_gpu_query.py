@@ -188,28 +188,35 @@ def test_query_more_segments_than_one_plan_pass(d):
     assert err <= ATTN_TOL, err
 
 
-def test_query_unknown_rows_hint_and_empty_context(d):
+# Blocks of up to 256 rows per segment may take the short kernels; 280 rows take
+# the long one, in two query tiles of which the second is partly filled.
+@pytest.mark.parametrize("n_q", [9, 70])
+def test_query_unknown_rows_hint_and_empty_context(d, n_q):
     """rows_hint 0 (split sized for long segments) with several segments that
     hold no context at all: those rows see only the tokens after it."""
     rng = np.random.default_rng(901)
-    got, want = _run(d, rng, 2, 2, 4, 3000, 128, 0.3, 1, 9, hint=0, empty_segments=2)
+    got, want = _run(d, rng, 2, 2, 4, 3000, 128, 0.3, 1, n_q, hint=0, empty_segments=2)
     err = row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128))
     assert err <= ATTN_TOL, err
 
 
-def test_query_large_logits(d):
+@pytest.mark.parametrize("T,n_q", [(2000, 20), (8000, 20), (2000, 70), (8000, 70)])
+def test_query_large_logits(d, T, n_q):
+    """Whole and split over key ranges."""
     rng = np.random.default_rng(902)
-    got, want = _run(d, rng, 1, 2, 4, 2000, 128, 0.5, 0, 20, sm_scale=3.0)
+    got, want = _run(d, rng, 1, 2, 4, T, 128, 0.5, 0, n_q, sm_scale=3.0)
     assert np.isfinite(got).all()
     assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= ATTN_TOL
 
 
+@pytest.mark.parametrize("T,n_q", [(3000, 24), (3000, 70), (700, 24), (700, 70)])
 @pytest.mark.parametrize("scale", [-0.7, 0.0])
-def test_query_negative_and_zero_scale(d, scale):
-    """The kernel scores with |scale| and negated queries for a negative
-    scale; a zero scale is uniform attention over the visible keys."""
+def test_query_negative_and_zero_scale(d, scale, T, n_q):
+    """The kernels score with |scale| and negated queries for a negative
+    scale; a zero scale is uniform attention over the visible keys.  Split over
+    key ranges (3,000 positions) and whole (700)."""
     rng = np.random.default_rng(907)
-    got, want = _run(d, rng, 1, 2, 4, 3000, 128, 0.5, 1, 24, sm_scale=scale)
+    got, want = _run(d, rng, 1, 2, 4, T, 128, 0.5, 1, n_q, sm_scale=scale)
     assert np.isfinite(got).all()
     assert row_rel_err(got.reshape(-1, 128), want.reshape(-1, 128)) <= ATTN_TOL
 
