@@ -259,7 +259,7 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t stream) {
   const dim3 grid(p.ntiles > 0 ? p.ntiles : 1, p.nseg);
   const bool whole = p.ntiles > 0 && rank_whole_segments(p.T, p.nseg);
   if (whole) {
-    hipLaunchKernelGGL(compact_rank_kernel, dim3(p.nseg), dim3(kSweepThreads), 0, stream, p);
+    hipLaunchKernelGGL(compact_rank_kernel, dim3(p.nseg), dim3(kRankThreads), 0, stream, p);
     hipLaunchKernelGGL(compact_scan_kernel<false>, dim3(1), dim3(kScanThreads), 0, stream, p);
   } else {
     if (p.ntiles > 0) hipLaunchKernelGGL(compact_count_kernel, grid, dim3(kThreads), 0, stream, p);

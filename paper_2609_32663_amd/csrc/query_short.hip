@@ -1,8 +1,8 @@
-// Query-block attention for short blocks: at most 128 query rows (tokens
-// x heads of a group) per segment, or kShortRows (256) over long segments.  What the rows compute is what
-// query_attn.hip computes; here the block is so short that reading K and V
-// bounds the call, so the kernel is a stream over the keys, split like the
-// decode step's, instead of 256-row query tiles.
+// Query-block attention for short blocks: at most 128 query rows (tokens x
+// heads of a group) per segment, or kShortRows (256) over long segments.  What
+// the rows compute is what query_attn.hip computes; here the block is so short
+// that reading K and V bounds the call, so the kernel is a stream over the
+// keys, split like the decode step's, instead of 256-row query tiles.
 //
 // Work split.  The keys of all segments are laid end to end (plus a fixed
 // cost per segment) and cut into P equal slices, one per workgroup; a slice
@@ -16,13 +16,14 @@
 //
 // Inside a workgroup the waves are RW row waves x KW key waves: a row wave
 // holds 32 rows (two 16-row groups), the key waves take 32-key tiles in turn.
-//   * K and V tiles go from memory straight into LDS, two tiles per key wave;
-//     the row waves of a key wave share its tiles and meet once per tile
-//     (with one row wave nothing meets in the stream);
+//   * K and V tiles go from memory straight into LDS, two or three tiles per
+//     key wave; the row waves of a key wave share its tiles and meet once per
+//     tile (with one row wave nothing meets in the stream);
 //   * scores, lazy running max, fp32 probabilities split into two bf16 parts
 //     and both products as in query_attn.hip.
-// At the end the key waves fold their states pairwise through LDS, in a
-// fixed order: every lane meets the lane that holds the same outputs.
+// At the end each key wave finishes its share of the output columns: the
+// others hand it theirs through LDS (every lane meets the lane that holds the
+// same outputs) and it adds them up in key-wave order.
 //
 // Why a kernel of its own: the 256-row tiles of query_attn.hip do the products
 // of all 256 rows whatever the block holds, in two rounds of workgroups after a
@@ -88,8 +89,9 @@ void query_short_kernel(QueryParams p) {
   // the key waves hand each other at the fold
   constexpr int S = short_stages<RW, KW, NT>();
   constexpr int kTile = KW * kSKeys * D;
-  __shared__ __align__(1024) uint16_t k0[kTile], k1[kTile], k2[S > 2 ? kTile : 8], k3[S > 3 ? kTile : 8];
-  __shared__ __align__(1024) uint16_t v0[kTile], v1[kTile], v2[S > 2 ? kTile : 8], v3[S > 3 ? kTile : 8];
+  static_assert(S == 2 || S == 3, "the ring's arrays");
+  __shared__ __align__(1024) uint16_t k0[kTile], k1[kTile], k2[S > 2 ? kTile : 8];
+  __shared__ __align__(1024) uint16_t v0[kTile], v1[kTile], v2[S > 2 ? kTile : 8];
   constexpr int OB = C::kBlocks / KW;  // 16-column output blocks that a key wave finishes
   constexpr int HB = KW == 1 ? 1 : (KW > 2 ? (OB + 1) / 2 : OB);  // handed over at a time
   __shared__ __align__(16) f32x4 fo[KW][RW][KW > 1 ? KW - 1 : 1][HB][kWave];
@@ -223,10 +225,8 @@ void query_short_kernel(QueryParams p) {
       __builtin_amdgcn_sched_barrier(0);
     };
 
-    uint16_t* const kb[4] = {k0 + kw * kSKeys * D, k1 + kw * kSKeys * D, S > 2 ? k2 + kw * kSKeys * D : k2,
-                             S > 3 ? k3 + kw * kSKeys * D : k3};
-    uint16_t* const vb[4] = {v0 + kw * kSKeys * D, v1 + kw * kSKeys * D, S > 2 ? v2 + kw * kSKeys * D : v2,
-                             S > 3 ? v3 + kw * kSKeys * D : v3};
+    uint16_t* const kb[3] = {k0 + kw * kSKeys * D, k1 + kw * kSKeys * D, S > 2 ? k2 + kw * kSKeys * D : k2};
+    uint16_t* const vb[3] = {v0 + kw * kSKeys * D, v1 + kw * kSKeys * D, S > 2 ? v2 + kw * kSKeys * D : v2};
 #pragma unroll
     for (int i = 0; i < S - 1; ++i) load(kb[i], vb[i], kw + i * KW);
 
