@@ -394,11 +394,11 @@ size_t dkv_query_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t num
  *          when that is 0 (keys too few to split).
  * Only DKV_BF16 is supported (DKV_ERR_UNSUPPORTED otherwise); head_dim 64 or
  * 128; DKV_ERR_UNSUPPORTED also when a dispatch would exceed 2^32 work-items
- * (512 per workgroup).  When the keys are split the call enqueues a one-workgroup plan
- * kernel (blocks of more than 256 query rows n_q * G per segment, of more than
- * 128 over segments of fewer than 8,192 rows on average, or of more than 512
- * segments), the attention kernel and a combine kernel; otherwise the
- * attention kernel alone.
+ * (512 per workgroup).  When the keys are split the call enqueues the attention
+ * kernel and a combine kernel, and before them a one-workgroup plan kernel
+ * unless the block is short (at most 256 query rows n_q * G per segment; of
+ * more than 64, where sizes and rows_hint say that the kernels for short blocks
+ * are no slower); otherwise the attention kernel alone.
  */
 dkv_status dkv_query_attn(dkv_dtype dtype, int32_t batch, int32_t num_q_heads,
                           int32_t num_kv_heads, int32_t head_dim, int32_t n_q, const void *q,

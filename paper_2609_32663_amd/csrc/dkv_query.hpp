@@ -58,11 +58,39 @@ QueryPlanShape query_plan_shape(int32_t nseg, int32_t rows, int32_t head_dim, in
 // workgroups' prefix over them shares the LDS with the tiles).
 constexpr int kShortRows = 256;
 constexpr int kShortSegments = 512;
-// Blocks of more than 128 rows leave one key wave and 133 KB of record per
-// piece, so they pay only over long segments: at this many keys per segment on
-// average.  Before / now, us, 240 rows: 8 segments of 11,500 keys 54.7 / 41.2,
-// of 45,000 121.3 / 87.1; 128 of 1,050 85.8 / 110.9, 480 of 1,430 193.6 / 280.4.
-constexpr int64_t kShortLongKeys = 8192;
+// Whether the short kernels take a call, where they are level or ahead; long /
+// short, us, attention and combine.
+//   * Up to 64 rows: always.
+//   * Up to 128 rows: but for many segments of few keys, where a piece is little
+//     more than its start and its record and the long kernel's items fit one
+//     round of workgroups or, with more than 96 rows, nearly fill two (128 rows
+//     of 64 dimensions: 128 segments of 960 keys 36 / 55, 80 of 1,400 33 / 41, 160
+//     of 1,400 58 / 69; a started second round turns it: 160 of 1,000 66 / 59, 96
+//     of 1,250 57 / 46; 65 rows, 256 unequal segments of 1,700 141 / 86).
+//   * More rows leave one key wave and up to 133 KB of record per piece, so the
+//     segments have to be long (240 rows: 128 segments of 1,050 keys 85.8 /
+//     110.9, 8 of 11,500 54.7 / 41.2) and few; with 128 dimensions the long
+//     kernel's overlapped products win again once all the keys are many (192
+//     rows: 8 segments of 120,000 199 / 180, 16 of 45,000 151 / 147, of 120,000
+//     341 / 371, 32 of 9,000 83 / 81, of 45,000 256 / 280, 128 of 9,000 214 /
+//     261; of 64 dimensions 32 of 45,000 203 / 196).
+constexpr int64_t kShortLongKeys = 8192;  // keys per segment on average
+constexpr int kShortManySegments = 48;
+constexpr int64_t kShortFewKeys = 2048;
+inline bool query_takes_short(int32_t nseg, int32_t rows, int32_t head_dim, int64_t rows_hint,
+                              const QueryPlanShape& sh) {
+  if (rows > kShortRows || nseg > kShortSegments) return false;
+  if (rows <= kShortRows / 4) return true;
+  if (rows <= kShortRows / 2) {
+    if (sh.plan_bytes == 0 || nseg < kShortManySegments || rows_hint <= 0 || rows_hint / kShortFewKeys >= nseg)
+      return true;
+    const int64_t tiles = (rows_hint / nseg + 63) / 64;  // of a segment, on average
+    const int64_t items = nseg * ((tiles + sh.tiles_per_range / 2) / sh.tiles_per_range);
+    return items > kQueryTargetItems / 2 && (items < 400 || rows <= 96);
+  }
+  return sh.plan_bytes > 0 && rows_hint / kShortLongKeys >= nseg && nseg <= 32 &&
+         (head_dim == 64 || rows_hint <= (int64_t(1) << 24) / nseg);
+}
 // K and V of a call up to this size may still be in the 256 MB last-level
 // cache from the call before (the block's append, the last step), so they are
 // loaded normally; larger ones are streamed past the caches.

@@ -92,10 +92,7 @@ dkv_status dkv_query_attn(dkv_dtype dtype, int32_t batch, int32_t num_q_heads, i
   p.max_items = (int32_t)sh.max_items;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
   p.out = out;
-  // blocks of more than 128 rows only where the keys are long (kShortLongKeys)
-  const bool few_rows = p.rows <= dkv::kShortRows / 2 ||
-                        (sh.plan_bytes > 0 && rows_hint / dkv::kShortLongKeys >= p.nseg);
-  if (p.rows <= dkv::kShortRows && few_rows && p.nseg <= dkv::kShortSegments) {
+  if (dkv::query_takes_short(p.nseg, p.rows, head_dim, rows_hint, sh)) {
     p.stream_once = rows_hint <= 0 || rows_hint > dkv::kShortCachedBytes / (4 * head_dim);
     if (sh.plan_bytes > 0) {
       // the workspace of the long-block split, laid out for the stream split:

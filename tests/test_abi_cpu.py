@@ -509,3 +509,59 @@ def test_copy_dispatch_stays_below_2_32_work_items(tmp_path):
         assert items < 1 << 32, (t, b)
         assert rows in (8192 // b, 32), (t, b)
         assert items >= 512 * (t // rows), (t, b)
+
+
+QUERY_ROUTE = r"""
+#include "dkv_query.hpp"
+#include <cstdio>
+int main() {
+  long long hint, tiles;
+  int nseg, rows, dim, split;
+  while (std::scanf("%d %d %d %lld %d %lld", &nseg, &rows, &dim, &hint, &split, &tiles) == 6) {
+    dkv::QueryPlanShape sh = {};
+    sh.plan_bytes = split ? 256 : 0;
+    sh.tiles_per_range = tiles;
+    std::printf("%d\n", dkv::query_takes_short(nseg, rows, dim, hint, sh) ? 1 : 0);
+  }
+}
+"""
+
+
+def _query_split(nseg, hint):
+    """(split over key ranges, 64-key tiles per range) of blocks of one query tile."""
+    tiles = -(-min(hint, 1 << 40) // 64) + nseg if hint > 0 else nseg * 512
+    return tiles >= nseg * 16, min(max(8, -(-tiles // 512)), 1 << 30)
+
+
+def test_query_blocks_take_the_faster_kernel(tmp_path):
+    """The route of query blocks at sizes where the two kernels' times are 5%
+    and more apart on an MI355X (equal segments), at the rule's edges, and for
+    hints at the ends of their range."""
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    rocm = "/opt/rocm/include"
+    if cxx is None or not os.path.isdir(rocm):
+        pytest.skip("no host compiler or HIP headers")
+    src = tmp_path / "route.cpp"
+    src.write_text(QUERY_ROUTE)
+    exe = tmp_path / "route"
+    subprocess.run([cxx, "-std=c++17", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}",
+                    f"-I{os.path.join(ROOT, 'paper_2609_32663_amd', 'csrc')}", str(src), "-o", str(exe)], check=True)
+    # (segments, query rows, head dim, keys and block tokens per segment, short kernel)
+    sizes = [(8, 4, 128, 45000, 1), (512, 64, 128, 1000, 1), (513, 4, 64, 1100, 0), (1, 257, 128, 9000, 0),
+             (64, 128, 64, 700, 1), (32, 128, 128, 1032, 1), (128, 128, 64, 992, 0), (128, 128, 128, 1032, 0),
+             (80, 128, 64, 1432, 0), (120, 80, 64, 1100, 0), (160, 128, 64, 1432, 0), (448, 112, 128, 988, 0),
+             (256, 65, 128, 1713, 1), (96, 128, 128, 1282, 1), (256, 128, 64, 2532, 1), (64, 128, 128, 4532, 1),
+             (128, 128, 128, 9032, 1), (2, 240, 128, 9060, 1), (8, 256, 128, 45064, 1), (12, 192, 128, 80048, 1),
+             (16, 192, 128, 120048, 0), (32, 256, 128, 45064, 0), (64, 192, 64, 9048, 0), (128, 256, 128, 9064, 0),
+             (512, 129, 128, 9129, 0), (128, 240, 128, 1110, 0), (32, 129, 64, 45129, 1)]
+    cases = [(n, r, d, n * k, *_query_split(n, n * k)) for n, r, d, k, _ in sizes]
+    want = [w for *_, w in sizes]
+    for hint in (0, -1, (1 << 63) - 1):
+        for n, r, w in ((1, 64, 1), (512, 128, 1), (1, 200, 0), (32, 256, 0)):
+            cases.append((n, r, 128, hint, *_query_split(n, hint)))
+            want.append(w)
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(str(int(x)) for x in c) for c in cases), check=True,
+                         capture_output=True, text=True).stdout.split()
+    assert [int(x) for x in out] == want, [c for c, x, w in zip(cases, out, want) if int(x) != w]
