@@ -19,6 +19,8 @@
 // Five launches (clear, three rounds, write); no launch depends on the host.
 // State lives in a caller-provided workspace.
 
+#include <type_traits>
+
 #include "dkv_device.hpp"
 #include "dkv_launch.hpp"
 
@@ -56,15 +58,19 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// A thread's share of one group of kTkGroup iterations: quadruple s is the
-// entries [i + s * kTkStep, + 4), those below `end`; the rest have valid = 0.
-// probs is 16-byte aligned and i a multiple of 4, so a whole quadruple is one
+typedef u32x4 __attribute__((aligned(4))) u32x4_words;  // the workspace is 4-byte aligned
+
+// A thread's share of one group of kTkGroup iterations from entry i0 on:
+// quadruple s is the entries [i0 + 4 tid + s * kTkStep, + 4), those below `end`;
+// the rest have valid = 0.
+// probs is 16-byte aligned and i0 a multiple of 4, so a whole quadruple is one
 // load; all of a group's loads are in flight together.
 struct KeyGroup {
   float4 x[kTkGroup];
   uint32_t valid[kTkGroup];
 
-  __device__ __forceinline__ void load(const float* probs, int64_t i, int64_t end) {
+  __device__ __forceinline__ void load(const float* probs, int64_t i0, int64_t end) {
+    const int64_t i = i0 + threadIdx.x * 4;
 #pragma unroll
     for (int s = 0; s < kTkGroup; ++s) {
       const int64_t at = i + (int64_t)s * kTkStep;
@@ -102,8 +108,19 @@ __device__ __forceinline__ void chunk_of(const TopkParams& p, int b, int64_t& c0
   c1 = c0 + p.chunk < p.n ? c0 + p.chunk : p.n;
 }
 
+// Runs `body` for a group of iterations: told at compile time that the group is
+// whole, or left to skip the iterations past the chunk (small exports are one
+// part of a group: 64 entries 20.7 us with all four iterations run, 18.3 with
+// one; large ones are whole groups, which the skips slow by 3%).
+template <class Body>
+__device__ __forceinline__ void whole_or_part(int64_t left, Body body) {
+  if (left >= kTkGroup * kTkStep) body(std::true_type{});
+  else body(std::false_type{});
+}
+
 __global__ __launch_bounds__(kTkThreads) void topk_init_kernel(TopkParams p) {
-  for (int i = blockIdx.x * kTkThreads + threadIdx.x; i < kTkWgHist; i += gridDim.x * kTkThreads) p.state[i] = 0u;
+  const int words = kTkHist + kTkRounds * p.copies * kTkMaxBins;
+  for (int i = blockIdx.x * kTkThreads + threadIdx.x; i < words; i += gridDim.x * kTkThreads) p.state[i] = 0u;
 }
 
 // The digit of round R: with the keys of round R's global histogram that
@@ -117,36 +134,41 @@ __device__ __forceinline__ void select_digit(const TopkParams& p, uint32_t& pref
                                              uint32_t* out) {
   constexpr int NB = 1 << kTkBits[R];
   constexpr int per = NB / kTkThreads;
-  __shared__ uint32_t bins[NB];
-  static_assert(NB % kTkThreads == 0, "bins spread evenly over the threads");
-  const uint32_t* g = p.state + kTkHist + R * kTkCopies * kTkMaxBins;
-  // the copies' sums, loaded coalesced (all loads in flight together) and
-  // handed over through LDS
+  static_assert(NB % kTkThreads == 0 && per % 4 == 0, "bins spread evenly over the threads, in whole loads");
+  // the copies' sums: a thread's bins are consecutive, so it loads each copy's
+  // by 16 bytes, all loads in flight together (handing the bins over through
+  // LDS took a round's 32 KiB of histograms past a quarter of the CU's LDS: with
+  // 1,024 workgroups, four a CU, round 1 of 82M entries ran 148 us where it is
+  // 80 otherwise)
+  const uint32_t* g = p.state + kTkHist + R * p.copies * kTkMaxBins + NB - per * (threadIdx.x + 1);
   uint32_t x[per];
   if (p.copies > 1) {
-    uint32_t y[kTkCopies][per];
+    u32x4 y[kTkCopies][per / 4];
 #pragma unroll
     for (int c = 0; c < kTkCopies; ++c)
 #pragma unroll
-      for (int j = 0; j < per; ++j) y[c][j] = g[c * kTkMaxBins + j * kTkThreads + threadIdx.x];
+      for (int v = 0; v < per / 4; ++v) y[c][v] = *reinterpret_cast<const u32x4_words*>(g + c * kTkMaxBins + 4 * v);
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-      x[j] = 0;
+    for (int v = 0; v < per / 4; ++v)
 #pragma unroll
-      for (int c = 0; c < kTkCopies; ++c) x[j] += y[c][j];
-    }
+      for (int e = 0; e < 4; ++e) {
+        x[4 * v + e] = 0;
+#pragma unroll
+        for (int c = 0; c < kTkCopies; ++c) x[4 * v + e] += y[c][v][e];
+      }
   } else {
 #pragma unroll
-    for (int j = 0; j < per; ++j) x[j] = g[j * kTkThreads + threadIdx.x];
-  }
+    for (int v = 0; v < per / 4; ++v) {
+      const u32x4 y = *reinterpret_cast<const u32x4_words*>(g + 4 * v);
 #pragma unroll
-  for (int j = 0; j < per; ++j) bins[j * kTkThreads + threadIdx.x] = x[j];
-  __syncthreads();
+      for (int e = 0; e < 4; ++e) x[4 * v + e] = y[e];
+    }
+  }
   uint32_t h[per];
   int64_t mine = 0;
 #pragma unroll
   for (int j = 0; j < per; ++j) {
-    h[j] = bins[NB - 1 - (per * threadIdx.x + j)];
+    h[j] = x[per - 1 - j];
     mine += h[j];
   }
   int64_t all;
@@ -180,7 +202,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_round_kernel(TopkParams p) {
   int64_t c0, c1;
   chunk_of(p, blockIdx.x, c0, c1);
   KeyGroup grp;
-  grp.load(p.probs, c0 + tid * 4, c1);
+  grp.load(p.probs, c0, c1);
   for (int i = tid; i < kTkWaves * NB; i += kTkThreads) (&hist[0][0])[i] = 0u;
   uint32_t prefix = 0u, need = (uint32_t)p.k;
   if constexpr (R > 0) {
@@ -197,19 +219,22 @@ __global__ __launch_bounds__(kTkThreads) void topk_round_kernel(TopkParams p) {
   __syncthreads();
   const uint32_t mask = R == 0 ? 0u : 0xFFFFFFFFu << ((shift + kTkBits[R]) & 31);
   for (int64_t i0 = c0; i0 < c1; i0 += kTkGroup * kTkStep) {
-    if (i0 > c0) grp.load(p.probs, i0 + tid * 4, c1);
+    if (i0 > c0) grp.load(p.probs, i0, c1);
+    whole_or_part(c1 - i0, [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < kTkGroup; ++s) {
-      uint32_t key[4];
-      grp.keys(s, key);
+      for (int s = 0; s < kTkGroup; ++s) {
+        if (!whole && i0 + s * kTkStep >= c1) continue;
+        uint32_t key[4];
+        grp.keys(s, key);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (((grp.valid[s] >> e) & 1u) && (key[e] & mask) == prefix)
-          atomicAdd(&hist[wave][(key[e] >> shift) & (NB - 1)], 1u);
-    }
+        for (int e = 0; e < 4; ++e)
+          if ((whole || ((grp.valid[s] >> e) & 1u)) && (key[e] & mask) == prefix)
+            atomicAdd(&hist[wave][(key[e] >> shift) & (NB - 1)], 1u);
+      }
+    });
   }
   __syncthreads();
-  uint32_t* g = p.state + kTkHist + (R * kTkCopies + blockIdx.x % p.copies) * kTkMaxBins;
+  uint32_t* g = p.state + kTkHist + (R * p.copies + blockIdx.x % p.copies) * kTkMaxBins;
   for (int i = tid; i < NB; i += kTkThreads) {
     uint32_t c = 0;
 #pragma unroll
@@ -226,7 +251,7 @@ __global__ __launch_bounds__(kTkThreads) void topk_write_kernel(TopkParams p) {
   int64_t c0, c1;
   chunk_of(p, blockIdx.x, c0, c1);
   KeyGroup grp;
-  grp.load(p.probs, c0 + tid * 4, c1);
+  grp.load(p.probs, c0, c1);
   // the last digit: thr is the K-th largest key, take the entries equal to
   // it that are kept
   uint32_t thr = 0u, take = 0u;
@@ -243,46 +268,54 @@ __global__ __launch_bounds__(kTkThreads) void topk_write_kernel(TopkParams p) {
   int64_t rank;  // the block's total
   block_exclusive_scan<kTkThreads>(before, red, &rank);
   for (int64_t i0 = c0; i0 < c1; i0 += kTkGroup * kTkStep) {
-    if (i0 > c0) grp.load(p.probs, i0 + tid * 4, c1);
+    if (i0 > c0) grp.load(p.probs, i0, c1);
     // ties per iteration, four 16-bit sums in one scan (an iteration holds at
     // most kTkStep of them)
     static_assert(kTkGroup == 4 && kTkStep < 65536, "four sums per scan");
-    uint32_t eq[kTkGroup];
-    uint64_t cnt = 0;
+    whole_or_part(c1 - i0, [&](auto whole) __attribute__((always_inline)) {
+      uint32_t eq[kTkGroup];
+      uint64_t cnt = 0;
 #pragma unroll
-    for (int s = 0; s < kTkGroup; ++s) {
-      uint32_t key[4];
-      grp.keys(s, key);
-      eq[s] = 0u;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) eq[s] |= (((grp.valid[s] >> e) & 1u) && p.k > 0 && key[e] == thr ? 1u : 0u) << e;
-      cnt |= (uint64_t)__popc(eq[s]) << (16 * s);
-    }
-    int64_t totals;
-    const uint64_t ex = (uint64_t)block_exclusive_scan<kTkThreads>((int64_t)cnt, red, &totals);
-#pragma unroll
-    for (int s = 0; s < kTkGroup; ++s) {
-      const int64_t i = i0 + (int64_t)s * kTkStep + tid * 4;
-      int64_t r = rank + (int64_t)((ex >> (16 * s)) & 0xFFFFu);
-      uint32_t key[4];
-      grp.keys(s, key);
-      uchar4 out;
-      uint8_t* ob = reinterpret_cast<uint8_t*>(&out);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool t = (eq[s] >> e) & 1u;
-        ob[e] = (p.k > 0 && ((grp.valid[s] >> e) & 1u) && (key[e] > thr || (t && r < (int64_t)take))) ? 1 : 0;
-        r += t ? 1 : 0;
-      }
-      if (grp.valid[s] == 0xFu) {
-        *reinterpret_cast<uchar4*>(p.pattern + i) = out;
-      } else {
+      for (int s = 0; s < kTkGroup; ++s) {
+        eq[s] = 0u;
+        if (!whole && i0 + s * kTkStep >= c1) continue;
+        uint32_t key[4];
+        grp.keys(s, key);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if ((grp.valid[s] >> e) & 1u) p.pattern[i + e] = ob[e];
+          eq[s] |= ((whole || ((grp.valid[s] >> e) & 1u)) && p.k > 0 && key[e] == thr ? 1u : 0u) << e;
+        cnt |= (uint64_t)__popc(eq[s]) << (16 * s);
       }
-      rank += (int64_t)(((uint64_t)totals >> (16 * s)) & 0xFFFFu);
-    }
+      int64_t totals;
+      const uint64_t ex = (uint64_t)block_exclusive_scan<kTkThreads>((int64_t)cnt, red, &totals);
+#pragma unroll
+      for (int s = 0; s < kTkGroup; ++s) {
+        if (!whole && i0 + s * kTkStep >= c1) continue;
+        const int64_t i = i0 + (int64_t)s * kTkStep + tid * 4;
+        int64_t r = rank + (int64_t)((ex >> (16 * s)) & 0xFFFFu);
+        uint32_t key[4];
+        grp.keys(s, key);
+        uchar4 out;
+        uint8_t* ob = reinterpret_cast<uint8_t*>(&out);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool t = (eq[s] >> e) & 1u;
+          ob[e] = (p.k > 0 && (whole || ((grp.valid[s] >> e) & 1u)) &&
+                   (key[e] > thr || (t && r < (int64_t)take)))
+                      ? 1
+                      : 0;
+          r += t ? 1 : 0;
+        }
+        if (whole || grp.valid[s] == 0xFu) {
+          *reinterpret_cast<uchar4*>(p.pattern + i) = out;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if ((grp.valid[s] >> e) & 1u) p.pattern[i + e] = ob[e];
+        }
+        rank += (int64_t)(((uint64_t)totals >> (16 * s)) & 0xFFFFu);
+      }
+    });
   }
 }
 
@@ -304,7 +337,7 @@ hipError_t launch_topk_pattern(TopkParams p, hipStream_t stream) {
   p.chunk = ((p.n + blocks - 1) / blocks + kTkStep - 1) / kTkStep * kTkStep;
   p.copies = blocks >= 64 ? kTkCopies : 1;
   if (p.k > 0) {
-    hipLaunchKernelGGL(topk_init_kernel, dim3(24), dim3(kTkThreads), 0, stream, p);
+    hipLaunchKernelGGL(topk_init_kernel, dim3(6 * p.copies), dim3(kTkThreads), 0, stream, p);
     hipLaunchKernelGGL(topk_round_kernel<0>, dim3(blocks), dim3(kTkThreads), 0, stream, p);
     hipLaunchKernelGGL(topk_round_kernel<1>, dim3(blocks), dim3(kTkThreads), 0, stream, p);
     hipLaunchKernelGGL(topk_round_kernel<2>, dim3(blocks), dim3(kTkThreads), 0, stream, p);

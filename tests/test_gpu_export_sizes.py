@@ -1,6 +1,7 @@
 """dkv_topk_pattern where its launch changes: entries just below, at and above
 64 workgroups' chunks of 4,096 (histogram copies from there on), ragged ends,
-and more entries than 1,024 workgroups' first groups hold.  Exact."""
+whole groups of iterations and parts of one, and more entries than 1,024
+workgroups' first groups hold.  Exact."""
 
 import numpy as np
 import pytest
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 63 * 4096), (1, 1, 63 * 4096 + 1), (1, 3, 87381 + 7), (7, 11, 13),
-                                   (5, 64, 16381)])
+                                   (1, 1, 1023), (1, 2, 512), (1, 1, 3073), (1, 1, 4095), (1, 1, 4096), (1, 1, 4097),
+                                   (1, 3, 2731), (5, 64, 16381)])
 @pytest.mark.parametrize("levels", [5, 1024, 1 << 30])
 def test_export_launch_sizes(shape, levels):
     import paper_2609_32663_amd as d
