@@ -172,9 +172,8 @@ size_t dkv_compact_workspace_bytes(const dkv_layout *layout);
  *            4 * N * Hkv * T: a position list per segment, plus per-tile
  *            counts), no initial contents required.
  * DKV_ERR_UNSUPPORTED when N * Hkv > 65535 or T > 268,435,424 (the copy
- * dispatch, a K and a V workgroup of 256 work-items per chunk of a segment's
- * T rows, must hold fewer than 2^32 work-items; chunks are 8 KiB of rows, and
- * 32 rows where shorter ones would be too many).
+ * dispatch, at most a K and a V workgroup of 256 work-items per 32 positions of
+ * a segment, must hold fewer than 2^32 work-items).
  * The dense cache may be freed once the stream has executed this call: that
  * is what realises the memory reduction.
  */

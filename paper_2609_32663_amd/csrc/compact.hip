@@ -11,9 +11,9 @@
 //           orders them in LDS and writes them, coalesced, to a per-segment
 //           list at their rank: list[s][r] is the position of packed row r;
 //   copy    a K and a V workgroup per (segment, 8 KiB chunk of packed
-//           rows): LPR lanes move one row with 16-byte non-temporal loads and
-//           stores (LPR = row bytes / 16), the source row being the list's
-//           entry.
+//           rows; up to two such chunks of 512-byte rows): LPR lanes move one
+//           row with 16-byte non-temporal loads and stores (LPR = row bytes /
+//           16), the source row being the list's entry.
 // Where one workgroup per segment can walk the whole mask row
 // (rank_whole_segments), compact_rank_kernel takes the place of count and
 // list: the mask is read once (the pack of 32 segments of 9,001 positions of 256
@@ -172,7 +172,15 @@ __global__ __launch_bounds__(kRankThreads) void compact_rank_kernel(CompactParam
   if (threadIdx.x == 0) p.tile_cnt[seg] = first;
 }
 
-template <int LPR, int ROWS>
+// ROWS: packed rows of a chunk; GRID: positions of a segment per K and V
+// workgroup of the grid.  With GRID = 2 ROWS the grid has workgroups for the
+// chunks up to rank T / 2, and each moves the chunk T / 2 further on too where the
+// segment reaches so far: most are as short as with a workgroup per chunk, but
+// segments that keep little leave half as many without work.  The whole pack of
+// 512-byte rows, us, 32-row chunks / 16-row chunks / 16-row chunks this way: 256
+// segments of 9,000 positions, 1% kept 40 / 70 / 40, 35% 286 / 268 / 273, 60% 474
+// / 445 / 466; 4,096 of 2,000, 1% 131 / 237 / 131, 35% 1,009 / 944 / 963.
+template <int LPR, int ROWS, int GRID>
 __global__ __launch_bounds__(kThreads) void compact_copy_kernel(CompactParams p) {
   constexpr int kRowsPerPass = kThreads / LPR;
   constexpr int kPasses = (ROWS + kRowsPerPass - 1) / kRowsPerPass;  // rows per lane group
@@ -182,38 +190,43 @@ __global__ __launch_bounds__(kThreads) void compact_copy_kernel(CompactParams p)
   const int seg = blockIdx.y;
   const int tid = threadIdx.x;
   const int lane = tid % LPR;
-  const int64_t r_lo = (int64_t)chunk * ROWS;
   // Most workgroups of the grid lie past their segment's rows: they leave
   // after one scalar load.
   const int32_t len = p.seg_len[seg];
-  if (len <= 0 || r_lo >= len) return;  // past the segment's rows, or not packed
-  const int64_t r_hi = r_lo + ROWS < len ? r_lo + ROWS : len;
-  const int32_t* list = p.list + (int64_t)seg * p.T;
-  int32_t pos[kPasses];
+  if (len <= 0) return;  // not packed
+  static_assert(GRID == ROWS || GRID == 2 * ROWS, "chunks of a workgroup");
+  const int chunks = GRID == ROWS ? 0 : (int)(copy_workgroups(p.T, GRID) / 2);  // of the first half
+  if (GRID != ROWS && chunk >= chunks) return;
+  for (int64_t r_lo = (int64_t)chunk * ROWS; r_lo < len; r_lo += (int64_t)chunks * ROWS) {
+    const int64_t r_hi = r_lo + ROWS < len ? r_lo + ROWS : len;
+    const int32_t* list = p.list + (int64_t)seg * p.T;
+    int32_t pos[kPasses];
 #pragma unroll
-  for (int u = 0; u < kPasses; ++u) {
-    const int64_t r = r_lo + tid / LPR + (int64_t)u * kRowsPerPass;
-    pos[u] = list[r < r_hi ? r : r_lo];
-  }
-  // Every list entry is waited for at once, then every row load is issued
-  // before any is waited for (rows past the chunk's end load its first
-  // row): waiting per row would also wait for the row loads before it.
-#pragma unroll
-  for (int u = 0; u < kPasses; ++u) asm volatile("" ::"v"(pos[u]));
-  const int64_t dst0 = p.seg_off[seg];
-  const int64_t src0 = (int64_t)seg * p.T;
-  const u32x4* src = reinterpret_cast<const u32x4*>(which ? p.v : p.k);
-  u32x4* dst = reinterpret_cast<u32x4*>(which ? p.v_out : p.k_out);
-  u32x4 rb[kPasses];
-#pragma unroll
-  for (int u = 0; u < kPasses; ++u) rb[u] = __builtin_nontemporal_load(&src[(src0 + pos[u]) * LPR + lane]);
-#pragma unroll
-  for (int u = 0; u < kPasses; ++u) {
-    const int64_t r = r_lo + tid / LPR + (int64_t)u * kRowsPerPass;
-    if (r < r_hi) {
-      __builtin_nontemporal_store(rb[u], &dst[(dst0 + r) * LPR + lane]);
-      if (which == 0 && lane == 0 && p.src_pos != nullptr) p.src_pos[dst0 + r] = pos[u];
+    for (int u = 0; u < kPasses; ++u) {
+      const int64_t r = r_lo + tid / LPR + (int64_t)u * kRowsPerPass;
+      pos[u] = list[r < r_hi ? r : r_lo];
     }
+    // Every list entry is waited for at once, then every row load is issued
+    // before any is waited for (rows past the chunk's end load its first
+    // row): waiting per row would also wait for the row loads before it.
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) asm volatile("" ::"v"(pos[u]));
+    const int64_t dst0 = p.seg_off[seg];
+    const int64_t src0 = (int64_t)seg * p.T;
+    const u32x4* src = reinterpret_cast<const u32x4*>(which ? p.v : p.k);
+    u32x4* dst = reinterpret_cast<u32x4*>(which ? p.v_out : p.k_out);
+    u32x4 rb[kPasses];
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) rb[u] = __builtin_nontemporal_load(&src[(src0 + pos[u]) * LPR + lane]);
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) {
+      const int64_t r = r_lo + tid / LPR + (int64_t)u * kRowsPerPass;
+      if (r < r_hi) {
+        __builtin_nontemporal_store(rb[u], &dst[(dst0 + r) * LPR + lane]);
+        if (which == 0 && lane == 0 && p.src_pos != nullptr) p.src_pos[dst0 + r] = pos[u];
+      }
+    }
+    if (GRID == ROWS) return;
   }
 }
 
@@ -267,16 +280,20 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t stream) {
   }
   if (p.ntiles > 0) {
     if (!whole) hipLaunchKernelGGL(compact_list_kernel, grid, dim3(kThreads), 0, stream, p);
-    const int rows = copy_rows(p.T, p.row_bytes);
-    auto copy = [&](auto kernel) {  // a K and a V workgroup per chunk
-      hipLaunchKernelGGL(kernel, dim3((uint32_t)copy_grid(p.T, rows, p.nseg), p.nseg), dim3(kThreads), 0, stream, p);
+    auto copy = [&](auto kernel) {  // K and V workgroups in turn
+      const int64_t n = copy_grid(p.T, copy_rows(p.row_bytes), p.nseg);
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)n, p.nseg), dim3(kThreads), 0, stream, p);
     };
     switch (p.row_bytes) {
-      case 128: copy(compact_copy_kernel<8, 64>); break;
-      case 256: copy(compact_copy_kernel<16, 32>); break;
+      case 128: copy(compact_copy_kernel<8, 64, 64>); break;
+      case 256: copy(compact_copy_kernel<16, 32, 32>); break;
       case 512:
-        if (rows == 16) copy(compact_copy_kernel<32, 16>);
-        else copy(compact_copy_kernel<32, 32>);
+        // a few long segments that keep little have too few chunks among their
+        // idle workgroups for the short ones to pay: 4 segments of 400,000
+        // positions, 5% kept 45 us with 32-row chunks, 55 with 16, 16 of 200,000
+        // 69 and 74 (64 of 131,072 158 and 162, 10% 309 and 299)
+        if (p.nseg < 32 && p.T > 131072) copy(compact_copy_kernel<32, 32, 32>);
+        else copy(compact_copy_kernel<32, 16, 32>);
         break;
       default: return hipErrorInvalidValue;
     }

@@ -171,7 +171,7 @@ dkv_status dkv_compact(const dkv_layout* layout, dkv_dtype dtype, const void* k,
   if (!head_dim_ok(L.head_dim)) return DKV_ERR_UNSUPPORTED;
   const int64_t nseg = (int64_t)L.num_units * L.num_kv_heads;
   if (nseg > 65535) return DKV_ERR_UNSUPPORTED;
-  // the copy dispatch, in 32-row chunks where shorter ones would be too many,
+  // the copy dispatch (at most a K and a V workgroup of 256 per 32 positions)
   // must hold fewer than 2^32 work-items
   if (!dkv::copy_dispatch_fits(L.context_len, dkv::kCopyRows)) return DKV_ERR_UNSUPPORTED;
   if (nseg == 0) return DKV_OK;

@@ -34,14 +34,14 @@ hipError_t launch_map_pattern(const MapParams& p, int num_segments, hipStream_t 
 
 // ---------------------------------------------------------------- compaction
 constexpr int kCompactTile = 4096;  // positions per compaction tile (count, scan and list)
-// Packed rows that one copy workgroup moves: 8 KiB of K or V (64 rows of 128
-// bytes, 32 of 256, 16 of 512).  Short workgroups copy fastest on this part
-// until their set-up dominates (4 layers of 8 x 131,072 rows, 35% kept, map and
-// pack: 128-byte rows 213 us with 16 rows, 156 with 32, 138 with 64, 145 with
-// 128; 256-byte rows 304, 255, 263, 277; two layers of 512-byte rows 259, 262,
-// 269, 273).  A dispatch holds fewer than 2^32 work-items (a K and a V
-// workgroup of 256 per chunk of a segment's T rows), so contexts for which 16
-// rows would not fit take 32, the form that the argument check counts.
+// The copy moves packed rows in chunks of 8 KiB of K or V (64 rows of 128
+// bytes, 32 of 256, 16 of 512): short workgroups copy fastest on this part until
+// their set-up dominates (4 layers of 8 x 131,072 rows, 35% kept, map and pack:
+// 128-byte rows 213 us with 16 rows, 156 with 32, 138 with 64, 145 with 128;
+// 256-byte rows 304, 255, 263, 277; two layers of 512-byte rows 259, 262, 269,
+// 273).  A dispatch holds fewer than 2^32 work-items; the argument check counts
+// a K and a V workgroup of 256 per 32 rows of a segment's T, and no row size
+// has more (rows of 512 bytes: two 16-row chunks a workgroup).
 constexpr int kCopyThreads = 256;
 constexpr int kCopyRows = 32;
 constexpr int64_t copy_workgroups(int64_t T, int rows) { return 2 * ((T + rows - 1) / rows); }
@@ -61,10 +61,8 @@ constexpr int64_t copy_grid(int64_t T, int rows, int64_t nseg) {
 constexpr bool copy_dispatch_fits(int64_t T, int rows) {
   return copy_workgroups(T, rows) * kCopyThreads <= (int64_t)UINT32_MAX;
 }
-constexpr int copy_rows(int64_t T, int row_bytes) {
-  const int rows = 8192 / row_bytes;
-  return copy_dispatch_fits(T, rows) ? rows : kCopyRows;
-}
+// Rows of a segment's T per K and V workgroup.
+constexpr int copy_rows(int row_bytes) { return row_bytes == 128 ? 2 * kCopyRows : kCopyRows; }
 
 struct CompactParams {
   const uint8_t* mask;     // [nseg][T]

@@ -476,7 +476,7 @@ int main() {
   long long T;
   int row_bytes;
   while (std::scanf("%lld %d", &T, &row_bytes) == 2) {
-    const int rows = dkv::copy_rows(T, row_bytes);
+    const int rows = dkv::copy_rows(row_bytes);
     std::printf("%d %lld\n", rows, (long long)dkv::copy_grid(T, rows, 65535) * 256);
   }
 }

@@ -100,7 +100,8 @@ def test_page_select_bound_rule(d, nseg, T):
                                               (1025, 1023, 64, torch.bfloat16), (1024, 1040, 64, torch.bfloat16),
                                               (127, 33000, 64, torch.bfloat16), (128, 33001, 64, torch.bfloat16),
                                               (128, 32784, 64, torch.bfloat16), (1025, 4096, 64, torch.bfloat16),
-                                              (1025, 4095, 64, torch.bfloat16), (128, 131072, 64, torch.bfloat16)])
+                                              (1025, 4095, 64, torch.bfloat16), (128, 131072, 64, torch.bfloat16),
+                                              (2, 131072, 128, torch.float32), (2, 131073, 128, torch.float32)])
 def test_compact_panels(d, nseg, T, dim, dtype):
     mask = _mask(nseg, T, T)
     k = torch.randn((1, nseg, T, dim), device=DEV).to(dtype)
@@ -127,9 +128,10 @@ def test_compact_panels(d, nseg, T, dim, dtype):
 @pytest.mark.parametrize("dim,dtype", [(64, torch.bfloat16), (64, torch.float32), (128, torch.bfloat16),
                                        (128, torch.float32)])
 def test_copy_chunk_edges(d, dim, dtype):
-    """Kept lengths around 16, 32, 64 and 128 rows, by mask and as a block
+    """Kept lengths around 16, 32, 64 and 128 rows, and around the 112 from
+    which workgroups move a second chunk of 512-byte rows, by mask and as a block
     gather (bins of one position: a chunk spans as many ranges as rows)."""
-    lens = [0, 1, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 190]
+    lens = [0, 1, 15, 16, 17, 31, 33, 63, 64, 65, 111, 112, 113, 127, 128, 129, 190, 207, 208, 209, 211]
     T, cap, nseg = 211, 2, len(lens)
     rng = np.random.default_rng(dim)
     pat = np.zeros((1, nseg, T), dtype=np.uint8)
