@@ -327,9 +327,10 @@ __global__ __launch_bounds__(kQThreads) void query_attn_kernel(QueryParams p) {
   // rescale of m, l and the accumulators (output rows of a lane are queries
   // 4kg + v of the group: their factors live in the lanes of those rows) run
   // only in waves where some lane does: 256 tokens of an 8B layer at 128K
-  // 306.5 -> 301.1 us a call, at 32K 109.1 -> 105.8, on one box (taking the
-  // bf16 remainders by dot products as well, 16 instructions fewer per half,
-  // gave 307 and 104: the kernel runs at the power limit).
+  // 259.4 -> 253.0 us a call, at 32K 99.9 -> 96.6 (medians of 20 turns, which
+  // spread by 1 to 2 us on either side; taking the bf16 remainders by dot products
+  // as well, 16 instructions fewer per half, gave nothing: the kernel runs at the
+  // power limit).
   auto softmax = [&](auto masked, float (&sc)[kRG][2][4], int64_t kh) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < kRG; ++q) {
