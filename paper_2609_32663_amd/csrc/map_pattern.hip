@@ -78,13 +78,17 @@ __device__ __forceinline__ void store_run(uint8_t* row, int32_t j0, int32_t T, b
 
 // ALIGNED: T is a multiple of 16, so every row starts on the 16-byte grid.
 // HEADS: the per-query-head masks are written too.
-// PAIRS: uniform bins of one or two positions.  A run then crosses eight to
+// WALK kEach: uniform bins of one or two positions.  A run then crosses eight to
 // sixteen, and a position's bin is a shift away, so it is walked position by
 // position, unrolled: 8 rows of 9,001 positions and one head each, bins of one
 // position, 25.8 us by regions, 20.2 by positions; with the per-head masks 33.9
 // and 21.6.  (From three positions on the walk by regions is as fast or faster.)
-template <bool ALIGNED, bool HEADS, bool PAIRS>
+// WALK kStep: other narrow bins (walk_step) with per-head masks, position by
+// position too, one bin down at each lower edge passed.
+enum Walk { kRegions, kEach, kStep };
+template <bool ALIGNED, bool HEADS, Walk WALK>
 __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
+  constexpr bool PAIRS = WALK != kRegions;
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ int64_t red[kMapThreads / kWave + 1];
   // heads that keep each position of a run of more than two regions
@@ -161,13 +165,24 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
     int k = -1;  // bin of the previous region (D: the uncovered part), or none
     [[maybe_unused]] uint32_t pair[kMapPerThread / 2];  // heads that keep positions 2i (low half) and 2i + 1
     if constexpr (PAIRS) {
+      [[maybe_unused]] int32_t lower = 0;  // lower edge of bin k
 #pragma unroll
       for (int x = 0; x < kMapPerThread; ++x) {
         const int32_t j = j0 + x, delta = Tn - 1 - j, u = delta - p.R;
         uint32_t bits = 0;
         if (j >= 0 && j < Tn) {
-          if (j < p.S || u < 0) bits = all_heads;
-          else if ((u >> (p.uniform_width - 1)) < D) bits = qbits[u >> (p.uniform_width - 1)];
+          if (j < p.S || u < 0) {
+            bits = all_heads;
+          } else if constexpr (WALK == kStep) {
+            // bins hold a position at least, so u passes one edge at most
+            if (k < 0 || u < lower) {
+              if (k >= 0) --k;
+              else k = find_bin(u, edges, D, p.uniform_width);
+              if (k < 0) k = D;
+              lower = p.uniform_width > 0 ? p.uniform_width * k : edges[k];
+            }
+            if (k < D) bits = qbits[k];
+          } else if ((u >> (p.uniform_width - 1)) < D) bits = qbits[u >> (p.uniform_width - 1)];
         }
         if (bits != 0u) keep |= 1u << x;
         if (x & 1) pair[x / 2] |= bits << 16;
@@ -264,6 +279,18 @@ __global__ __launch_bounds__(kMapThreads) void map_pattern_kernel(MapParams p) {
 
 }  // namespace
 
+// Bins so narrow that a run crosses several and their heads are picked apart
+// position by position anyway; bins that cover little of the row leave most runs
+// uniform.  16 groups of 8 heads, regions / positions, us: 688 positions, bins of
+// 3 on average 9.5 / 7.1; 1,500 positions, of 2 15.2 / 11.1 (14.3 before the walk
+// by regions); one head, 1,000 positions, of 4 9.8 / 7.1.  Equal bins of three:
+// 4,000 rows of 30,000, one head each, 233 / about 200 (198 before the walk), 168
+// rows, four heads each, 39.9 / 42.3 (66 before); of four and more: regions.
+static bool walk_step(const MapParams& p) {
+  if (p.uniform_width > 0) return p.uniform_width == 3;
+  return p.edges[p.D] <= 6 * p.D && 2 * (int64_t)p.edges[p.D] >= p.T;
+}
+
 int64_t map_blocks(int32_t T, int64_t num_segments) { return map_chunks(T) * num_segments; }
 
 hipError_t launch_map_pattern(const MapParams& p, int num_segments, hipStream_t stream) {
@@ -277,8 +304,9 @@ hipError_t launch_map_pattern(const MapParams& p, int num_segments, hipStream_t 
     const bool aligned = (p.T & 15) == 0;
     auto bins = [&](auto al, auto hd) {
       constexpr bool A = decltype(al)::value, H = decltype(hd)::value;
-      if (p.uniform_width == 1 || p.uniform_width == 2) map(map_pattern_kernel<A, H, true>);
-      else map(map_pattern_kernel<A, H, false>);
+      if (p.uniform_width == 1 || p.uniform_width == 2) map(map_pattern_kernel<A, H, kEach>);
+      else if (H && walk_step(p)) map(map_pattern_kernel<A, H, H ? kStep : kRegions>);
+      else map(map_pattern_kernel<A, H, kRegions>);
     };
     if (p.q_mask != nullptr) aligned ? bins(std::true_type{}, std::true_type{}) : bins(std::false_type{}, std::true_type{});
     else aligned ? bins(std::true_type{}, std::false_type{}) : bins(std::false_type{}, std::false_type{});

@@ -247,6 +247,30 @@ def test_map_heads(d, G, T, width):
         np.testing.assert_array_equal(n.cpu().numpy(), want_len)
 
 
+@pytest.mark.parametrize("G", [1, 3, 8])
+@pytest.mark.parametrize("T,D,span", [(17, 6, 17), (700, 340, 690), (1500, 500, 1100), (1500, 500, 760),
+                                      (1504, 240, 1440), (1504, 240, 1441), (2049, 512, 1024),
+                                      (2049, 512, 1025), (3000, 512, 3000)])
+def test_map_narrow_unequal_bins(d, G, T, D, span):
+    """Narrow bins of unequal widths, with a head's mask or without: either side
+    of the rule that walks them position by position (six positions on average,
+    half the row covered), uncovered ends, and contexts shorter than the row."""
+    rng = np.random.default_rng([G, T, D, span])
+    edges = [0] + sorted(rng.choice(np.arange(1, span), D - 1, replace=False).tolist()) + [span]
+    Hkv, S, R = 2, 3, 7
+    lens = np.array([T, T - 5, 0, T // 3], dtype=np.int32)
+    pat = (rng.random((4, Hkv * G, D)) < 0.4).astype(np.uint8)
+    lay = d.make_layout(4, Hkv * G, Hkv, 64, T, S, R, edges)
+    kv = torch.full((4, Hkv, T), 9, dtype=torch.uint8, device=DEV)
+    qm = torch.full((4, Hkv * G, T), 9, dtype=torch.uint8, device=DEV)
+    n = torch.empty((4, Hkv), dtype=torch.int32, device=DEV)
+    d.dkv_map_pattern_ragged(lay, torch.from_numpy(lens).to(DEV), torch.from_numpy(pat).to(DEV), kv, n, qm)
+    want_q, want, want_len = o.map_pattern(pat, T, S, R, edges, Hkv, unit_len=lens)
+    np.testing.assert_array_equal(qm.cpu().numpy(), want_q)
+    np.testing.assert_array_equal(kv.cpu().numpy(), want)
+    np.testing.assert_array_equal(n.cpu().numpy(), want_len)
+
+
 @pytest.mark.parametrize("dim,dtype,T", [(64, torch.bfloat16, 1024), (64, torch.bfloat16, 4096), (64, torch.bfloat16, 4097),
                                          (128, torch.bfloat16, 128), (128, torch.bfloat16, 2048), (128, torch.float32, 64),
                                          (128, torch.float32, 1024), (128, torch.float32, 100)])
