@@ -13,7 +13,7 @@
 // a page.  Short contexts, and longer ones with enough segments
 // (select_whole_segments), take one workgroup per segment and one pass over the
 // mask (page_select_kernel): 256 segments of 131,072 positions, map included,
-// took 49.7 us in the two passes below and take 25.8 (14.0 for the selection
+// took 49.4 us in the two passes below and take 25.0 (13.4 for the selection
 // alone, against 39).  With fewer or longer segments one workgroup each would
 // leave the chip idle; those take two passes over the (segment, 4096-position
 // tile) grid:
